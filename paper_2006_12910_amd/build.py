@@ -15,7 +15,8 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "liblb.so")
 SOURCES = ["lb_api.hip", "common.hip", "kern_f64.hip", "kern_f32.hip", "kern_f16.hip",
-           "kern_bf16.hip", "lb3_api.hip"]
+           "kern_bf16.hip", "lb3_api.hip", "kern3_f64.hip", "kern3_f32.hip",
+           "kern3_f16.hip", "kern3_bf16.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 # No floating-point contraction: a node's arithmetic then compiles to the same
@@ -47,7 +48,7 @@ def _compile(src: str, verbose: bool) -> str:
     return obj
 
 
-def build(verbose: bool = False, jobs: int = 6) -> str:
+def build(verbose: bool = False, jobs: int = 8) -> str:
     os.makedirs(BUILD, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))

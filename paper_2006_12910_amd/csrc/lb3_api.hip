@@ -10,7 +10,7 @@
 #include <vector>
 
 #include "lb.h"
-#include "sweep3_impl.h"
+#include "launch3.h"
 
 using namespace lbk3;
 
@@ -33,6 +33,12 @@ lb_status fail3(lb_status s, const std::string &msg) { return lbk::lb_fail(s, ms
   } while (0)
 
 size_t al256(size_t v) { return (v + 255) & ~size_t(255); }
+
+// The sweep streams past the 256 MB last-level cache when both buffers exceed
+// it by half (192 x 192 x nz, us a step cached / streaming at 290, 360, 400,
+// 450 MB: FP32 57.8 / 58.3, 73.0 / 73.5, 78.4 / 74.4, 92.9 / 84.4; FP64 with
+// noise 54.5 / 60.0, 72.1 / 76.6, 76.8 / 76.8, 92.3 / 87.5).
+constexpr size_t STREAM_MIN_BYTES = size_t(384) << 20;
 
 // nodes per host-transfer band (initial fields, moments, populations)
 constexpr long long BAND = 262144;
@@ -215,45 +221,12 @@ lb_status push_desc3(lb3_domain *d) {
 
 namespace {
 
-template <int ST, int Q, bool PL, int NZ>
-void launch_sweep3_qn(const lb3_domain *d, unsigned blocks, int k) {
-  const dim3 g(blocks), b(256);
-  if (d->L.solids) {
-    if (d->wide)
-      hipLaunchKernelGGL((k_sweep3<ST, true, true, Q, PL, NZ>), g, b, 0, d->stream, d->ddesc(), k);
-    else
-      hipLaunchKernelGGL((k_sweep3<ST, true, false, Q, PL, NZ>), g, b, 0, d->stream, d->ddesc(), k);
-  } else {
-    if (d->wide)
-      hipLaunchKernelGGL((k_sweep3<ST, false, true, Q, PL, NZ>), g, b, 0, d->stream, d->ddesc(), k);
-    else
-      hipLaunchKernelGGL((k_sweep3<ST, false, false, Q, PL, NZ>), g, b, 0, d->stream, d->ddesc(), k);
-  }
-}
-template <int ST, int Q, bool PL> void launch_sweep3_q(const lb3_domain *d, unsigned blocks, int k) {
-  // noise kind: none, with BGK, with TRT (the last needs more registers)
-  if (!d->hd.noise) launch_sweep3_qn<ST, Q, PL, 0>(d, blocks, k);
-  else if (d->hd.trt) launch_sweep3_qn<ST, Q, PL, 2>(d, blocks, k);
-  else launch_sweep3_qn<ST, Q, PL, 1>(d, blocks, k);
-}
-template <int ST> void launch_sweep3_st(const lb3_domain *d, unsigned blocks, int k) {
-  const bool pl = d->desc.power_law != 0;
-  if (d->q == 27) {
-    if (pl) launch_sweep3_q<ST, 27, true>(d, blocks, k);
-    else launch_sweep3_q<ST, 27, false>(d, blocks, k);
-  } else {
-    if (pl) launch_sweep3_q<ST, 19, true>(d, blocks, k);
-    else launch_sweep3_q<ST, 19, false>(d, blocks, k);
-  }
-}
-
 void launch_sweep3(const lb3_domain *d, unsigned blocks, int k) {
-  switch (d->desc.storage) {
-    case LB_F64: launch_sweep3_st<0>(d, blocks, k); break;
-    case LB_F32: launch_sweep3_st<1>(d, blocks, k); break;
-    case LB_F16_DELTA: launch_sweep3_st<2>(d, blocks, k); break;
-    default: launch_sweep3_st<3>(d, blocks, k); break;
-  }
+  auto *sweep = d->desc.storage == LB_F64         ? sweep3_f64
+                : d->desc.storage == LB_F32       ? sweep3_f32
+                : d->desc.storage == LB_F16_DELTA ? sweep3_f16
+                                                  : sweep3_bf16;
+  sweep(d->hd, d->ddesc(), d->q, d->wide, blocks, k, d->stream);
 }
 
 }  // namespace
@@ -311,6 +284,8 @@ static lb_status lb3_create_domain_impl(const lb3_domain_desc *desc, void *dev_w
   h.key1 = (uint32_t)(desc->seed >> 32);
   h.tiles_x = (desc->nx + 63) / 64;
   h.tiles_y = (desc->ny + 3) / 4;
+  h.stream = 2.0 * d->q * desc->nz * desc->ny * L.pitch * (double)elem_of(desc->storage) >=
+             (double)STREAM_MIN_BYTES;
   h.rho0 = desc->rho0;
   // with the power law tau is the local tau*; the domain-wide values below
   // are those of tau_min (unused by the sweep)
@@ -418,9 +393,8 @@ static lb_status lb3_step_impl(lb3_domain *d, int64_t nsteps) {
   const unsigned blocks = (unsigned)(d->hd.tiles_x * d->hd.tiles_y * d->desc.nz);
   for (int64_t k0 = 0; k0 < nsteps; k0 += 1024) {
     const int c = (int)std::min<int64_t>(1024, nsteps - k0);
-    for (int k = 0; k < c; ++k) {
-      launch_sweep3(d, blocks, k);
-    }
+    int k = 0;
+    for (; k < c; ++k) launch_sweep3(d, blocks, k);
     hipLaunchKernelGGL(k_advance3, dim3(1), dim3(1), 0, d->stream, d->ddesc(), c);
     HIPCHK3(hipGetLastError());
   }

@@ -74,6 +74,7 @@ struct Dom3 {
   int sr;              // 16-bit storage rounds stochastically
   uint32_t key0, key1; // rounding-bit key
   int tiles_x, tiles_y;  // 64 x 4 node tiles of one z plane
+  int stream;            // 1: the buffers exceed the last-level cache (M3_STREAM)
   int trt;               // two relaxation times (else BGK: tau_m = tau)
   double rho0, tau, omega, gx, gy, gz;
   double tau_m, omega_m;  // relaxation of the antisymmetric parts
@@ -329,6 +330,18 @@ __device__ __forceinline__ void noise3(const Dom3 &D, uint32_t node, uint32_t st
   }
 }
 
+// e_i . v.  The zero components are left out at compile time: without
+// fast-math the compiler must keep 0 * v and its sum (48 of the 335 vector
+// instructions of an FP32 D3Q19 node).
+template <class R> __device__ __forceinline__ R dot3(int i, R vx, R vy, R vz) {
+  const R a = ex(i) < 0 ? -vx : vx, b = ey(i) < 0 ? -vy : vy, c = ez(i) < 0 ? -vz : vz;
+  if (ex(i) && ey(i) && ez(i)) return a + b + c;
+  if (ex(i) && ey(i)) return a + b;
+  if (ex(i) && ez(i)) return a + c;
+  if (ey(i) && ez(i)) return b + c;
+  return ex(i) ? a : (ey(i) ? b : c);
+}
+
 // BGK or TRT collision of one node in deviation form.  The equilibrium of
 // Eq. LB2 with u = J / rho, J = j + rho tau_m g (tau_m = tau for BGK):
 // opposite velocities share the even part c and take c +- 3 w (e.J); the
@@ -340,9 +353,12 @@ __device__ __forceinline__ void noise3(const Dom3 &D, uint32_t node, uint32_t st
 // increments before the one final rounding, as the D2Q9 sweep does (the
 // momentum term of the stored values would otherwise round the body force
 // of slow flows with a bias).
-// NZ: no noise (0), noise with BGK (1) or with TRT (2)
-template <class R, int Q, bool PL, int NZ>
+// NZ: no noise (0), noise with BGK (1) or with TRT (2).  TR: the collision
+// kind, BGK (0), TRT (1) or the domain's (-1, a uniform branch, which keeps
+// the values of both kinds in registers).
+template <class R, int Q, bool PL, int NZ, int TR = -1>
 __device__ __forceinline__ void collide3(const Dom3 &D, R d[Q], uint32_t node, uint32_t step) {
+  const bool trt = TR < 0 ? D.trt != 0 : TR == 1;
   R drho = d[0];
 #pragma unroll
   for (int i = 1; i < Q; i += 2) drho += d[i] + d[i + 1];
@@ -366,7 +382,7 @@ __device__ __forceinline__ void collide3(const Dom3 &D, R d[Q], uint32_t node, u
     const R inv[4] = {R(1), R(1), R(1), R(1)};
     const R ts = tau_power3<R>(D, shear_measure3<R, Q>(D, ps, inv, drho, rho, irho, jx, jy, jz));
     om = R(1) / ts;
-    if (D.trt) {
+    if (trt) {
       tau = R(0.5) + par3<R>(D.magic, D.magic_f) / (ts - R(0.5));
       omm = R(1) / tau;
     } else {
@@ -384,8 +400,7 @@ __device__ __forceinline__ void collide3(const Dom3 &D, R d[Q], uint32_t node, u
 #pragma unroll
   for (int i = 1; i < Q; i += 2) {
     const R w = w3<R>(Q, i);
-    const R eu = R(ex(i)) * ux + R(ey(i)) * uy + R(ez(i)) * uz;
-    const R eJ = R(ex(i)) * Jx + R(ey(i)) * Jy + R(ez(i)) * Jz;
+    const R eu = dot3<R>(i, ux, uy, uz), eJ = dot3<R>(i, Jx, Jy, Jz);
     const R c = w * (drho + fmr(r45 * eu, eu, -q));
     const R l = (R(3) * w) * eJ;
     eq[i] = c + l;
@@ -393,7 +408,7 @@ __device__ __forceinline__ void collide3(const Dom3 &D, R d[Q], uint32_t node, u
   }
   if constexpr (sizeof(R) == 4) {
     R inc[Q];
-    if (D.trt) {
+    if (trt) {
 #pragma unroll
       for (int i = 1; i < Q; i += 2) {
         const R a = eq[i] - d[i], b = eq[i + 1] - d[i + 1];
@@ -441,7 +456,7 @@ __device__ __forceinline__ void collide3(const Dom3 &D, R d[Q], uint32_t node, u
 #pragma unroll
     for (int i = 1; i < Q; i += 2) s += eq[i] + eq[i + 1];
     eq[0] = drho - s;
-    if (D.trt) {
+    if (trt) {
       d[0] = fmr(om, eq[0] - d[0], d[0]);
 #pragma unroll
       for (int i = 1; i < Q; i += 2) {
@@ -583,17 +598,33 @@ __device__ __forceinline__ void collide3_scaled(const Dom3 &D, float d[Q], uint3
   }
 }
 
-// XCD-aware block order: the hardware deals consecutive block ids to the 8
-// XCDs in turn; remapped, each XCD walks a contiguous run of tiles, so the
-// 128-byte lines that an x-shifted pull shares with the neighbouring tile
-// are found in the same L2 (without it the FP32 256^3 sweep read 1.26 x its
-// populations).
-__device__ __forceinline__ int xcd_order(int bid, int nblocks) {
+// XCD-aware block order.  The hardware deals consecutive block ids to the 8
+// XCDs in turn; the 128-byte lines that an x-shifted pull shares with the
+// neighbouring tile should be found in the same L2 (dealt as they come, the
+// FP32 256^3 sweep read 1.26 x its populations).
+//
+// Buffers that the last-level cache mostly holds: each XCD walks one contiguous run of
+// tiles (64^3 FP32 7.9 us a step, against 8.7 as dealt and 9.4 in the order
+// below).  Larger ones, read from HBM: each XCD takes runs of 8 tiles, so
+// that the whole chip works on one part of the lattice at a time, and the
+// stores go past the caches (a line is read again only after the caches have
+// been written several times over).  192 x 192 x 130, contiguous runs and
+// cached stores against this: FP32 D3Q19 149 -> 136 us a step (4.9 -> 5.4
+// TB/s), FP16 D3Q19 82 -> 73, FP16 D3Q27 108 -> 92, FP32 with noise 151 ->
+// 139, FP64 283 -> 270; runs of 1 / 32 tiles FP16 D3Q27 93 / 95, the order
+// alone 96, the stores alone 104.
+template <bool STREAM> __device__ __forceinline__ int tile_order3(int bid, int nblocks) {
   constexpr int NX = 8;
-  if (nblocks < 2 * NX) return bid;
-  const int xcd = bid % NX, local = bid / NX;
-  const int per = nblocks / NX, rem = nblocks % NX;
-  return xcd * per + (xcd < rem ? xcd : rem) + local;
+  if constexpr (STREAM) {
+    constexpr int G = NX * 8;
+    const int in = bid % G;
+    return bid - in + G > nblocks ? bid : bid - in + (in % NX) * 8 + in / NX;
+  } else {
+    if (nblocks < 2 * NX) return bid;
+    const int xcd = bid % NX, local = bid / NX;
+    const int per = nblocks / NX, rem = nblocks % NX;
+    return xcd * per + (xcd < rem ? xcd : rem) + local;
+  }
 }
 
 // Raw buffer access: the memory unit adds a wave-uniform (scalar) and a
@@ -612,16 +643,25 @@ template <class T> __device__ __forceinline__ T ld3(Res3 r, uint32_t voff, uint3
   else
     return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, 0));
 }
-template <class T> __device__ __forceinline__ void st3(Res3 r, uint32_t voff, uint32_t soff, T v) {
+// NT: non-temporal (cache-policy bit 2)
+template <class T, bool NT>
+__device__ __forceinline__ void st3(Res3 r, uint32_t voff, uint32_t soff, T v) {
+  constexpr int aux = NT ? 2 : 0;
   if constexpr (sizeof(T) == 2) {
-    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), r, (int)voff, (int)soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), r, (int)voff, (int)soff, aux);
   } else if constexpr (sizeof(T) == 4) {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (int)voff, (int)soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (int)voff, (int)soff, aux);
   } else {
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)voff, (int)soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)voff, (int)soff, aux);
   }
 }
+
+// Forms of the sweep: 32-bit byte offsets with the buffers mostly in the
+// last-level cache, 32-bit offsets streaming past it (see tile_order3), or
+// 64-bit offsets.  A template parameter: chosen at run time, the second copy
+// of the stores cost the FP64 noise sweep 12 % and small lattices 1-2 %.
+enum : int { M3_CACHED = 0, M3_STREAM = 1, M3_WIDE = 2 };
 
 // One step of every node: 256 threads = a tile of 64 (x) by 4 (y) nodes of
 // one z plane; each wave reads 64 consecutive x of a row per population
@@ -631,7 +671,7 @@ template <class T> __device__ __forceinline__ void st3(Res3 r, uint32_t voff, ui
 // step and never pulled).  Addressing: each direction pair (i odd, i + 1)
 // loads at the pair's first population plane (a wave-uniform offset) plus a
 // per-lane byte offset, and stores at its own plane plus the node's offset;
-// with WIDE false (Q population planes below 2^32 bytes) these are raw
+// except with M3_WIDE (Q population planes of 2^32 bytes and more) these are raw
 // buffer accesses, and a pulled population costs one vector add for its
 // address.  A bounced link reads the opposite population of the node itself,
 // from the same pair base.  SOLIDS false: no node words (no walls or
@@ -644,17 +684,18 @@ constexpr int sweep3_waves(int st, int q, bool pl, bool noise) {
   return noise && base > cap ? cap : base;
 }
 
-template <int ST, bool SOLIDS, bool WIDE, int Q, bool PL, int NZ>
+template <int ST, bool SOLIDS, int MODE, int Q, bool PL, int NZ>
 __global__ __launch_bounds__(256, sweep3_waves(ST, Q, PL, NZ != 0)) void k_sweep3(const Dom3 *__restrict__ Dp, int kstep) {
   using S = S3<ST>;
   using T = typename S::T;
   using R = typename S::R;
+  constexpr bool WIDE = MODE == M3_WIDE;
   using Off = typename std::conditional<WIDE, uint64_t, uint32_t>::type;
   constexpr Off E = sizeof(T);
   const Dom3 &D = *Dp;
   const int nx = D.nx, ny = D.ny, nz = D.nz, pitch = D.pitch;
   const int per_plane = D.tiles_x * D.tiles_y;
-  const int b = xcd_order((int)blockIdx.x, (int)gridDim.x);
+  const int b = tile_order3<MODE != M3_CACHED>((int)blockIdx.x, (int)gridDim.x);
   const int z = b / per_plane;
   const int t = b - z * per_plane;
   const int ty = t / D.tiles_x, tx = t - ty * D.tiles_x;
@@ -732,7 +773,7 @@ __global__ __launch_bounds__(256, sweep3_waves(ST, Q, PL, NZ != 0)) void k_sweep
     if constexpr (WIDE)
       *(LBK_GLOBAL T *)(dst + (Off)i * popb + here) = v;
     else
-      st3<T>(rd, here, __builtin_amdgcn_readfirstlane((uint32_t)i * popb), v);
+      st3<T, MODE == M3_STREAM>(rd, here, __builtin_amdgcn_readfirstlane((uint32_t)i * popb), v);
   }
 }
 
@@ -893,7 +934,7 @@ __global__ __launch_bounds__(256) void k_mass3_partial(const Dom3 *__restrict__ 
   if (threadIdx.x == 0) D.partials[z] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-__global__ __launch_bounds__(64) void k_mass3_final(const Dom3 *__restrict__ Dp) {
+static __global__ __launch_bounds__(64) void k_mass3_final(const Dom3 *__restrict__ Dp) {
   const Dom3 &D = *Dp;
   double s = 0.0;
   for (int i = (int)threadIdx.x; i < D.nz; i += 64) s += D.partials[i];
@@ -905,6 +946,6 @@ __global__ __launch_bounds__(64) void k_mass3_final(const Dom3 *__restrict__ Dp)
   }
 }
 
-__global__ void k_advance3(const Dom3 *__restrict__ Dp, int n) { *Dp->tstep += (uint64_t)n; }
+static __global__ void k_advance3(const Dom3 *__restrict__ Dp, int n) { *Dp->tstep += (uint64_t)n; }
 
 }  // namespace lbk3
