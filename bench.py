@@ -5,21 +5,21 @@ Workload (precision-and-batching stress): one 8192x8192 periodic domain plus
 200 uneven periodic domains of 64^2..2048^2 (log-uniform sides, RSA disc
 obstacles at 20% solid, tau ~ U[0.55, 1.2]), all started from seeded shear
 waves (u0 = 0.01).  Every step advances all 201 domains with one sweep launch
-(batched, replayed from a hipGraph).  Populations are stored as FP16 deviations
+(batched).  Populations are stored as FP16 deviations
 with stochastic rounding (the reported value), and, for comparison, as plain
 FP32 and as BF16 deviations; arithmetic is FP32.  Each launch of the
-two-step sweep advances every domain by two steps; before the timed region
-lb_batch_autotune picks its tile height (timed once per process, then
-cached).  With --single-step (one step per launch) the single-step tile
-shapes are tuned instead, on a throwaway copy of the batch.  The first call
-captures every step graph the timed calls replay.
+multi-step sweep advances every domain by 3, 5, 7 or 9 steps (the library
+picks the count from the batch's sizes).  With --single-step (one step per
+launch, replayed from a hipGraph that the first call captures) the tile shapes
+are tuned before the timed region, on a throwaway copy of the batch.
 
 MLUPS counts every lattice site of every domain (solids included), as the
 paper defines it.  The roofline object reports the sweep kernel's algorithmic
-HBM bytes per launch over its measured average launch duration against 8 TB/s
+HBM bytes per step over its measured average duration per step against 8 TB/s
 (HIP events on the launch stream; the duration is the difference between a
 call of 2K steps and the timed call of K steps, which removes each call's
-fixed cost, the FP64 density sums).  The CPU baseline is the FP64 oracle on a
+fixed cost, the FP64 density sums).  With several steps per launch that is an
+effective rate: the populations cross the memory once per launch.  The CPU baseline is the FP64 oracle on a
 bounded sample of the smallest domains of the same workload, 1000 steps each,
 on all host threads the process may use (at most 16) and on one thread, and on
 a few steps of each other workload's lattice; the same sample, run on the GPU
@@ -51,7 +51,7 @@ SHEAR_U0 = 0.01
 STORAGE_BYTES = {"f16": 2, "bf16": 2, "f32": 4}
 ROUNDING = {"f16": "stochastic", "bf16": "stochastic", "f32": "nearest"}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sweep_traffic.json")
-SWEEP_SOURCES = ["paper_2006_12910_amd/csrc/sweep_impl.h", "paper_2006_12910_amd/csrc/sweep2_impl.h",
+SWEEP_SOURCES = ["paper_2006_12910_amd/csrc/sweep_impl.h", "paper_2006_12910_amd/csrc/sweepn_impl.h",
                  "paper_2006_12910_amd/csrc/lb_device.h", "paper_2006_12910_amd/csrc/kernels_st.h",
                  "paper_2006_12910_amd/csrc/lb_api.hip", "paper_2006_12910_amd/build.py"]
 
@@ -212,8 +212,7 @@ def run_variant(storage, specs, masks, steps, warmup, tune, fixed_tiles=None, tw
     uses, so nothing is captured inside the timed call).  With single steps
     the autotuner picks the members' tile shapes.  Also
     returns the ms of a following call of 2 * steps steps.  An untimed call
-    of `steps` steps precedes the timed one.  With the two-step sweep the
-    batch's tile height comes from lb_batch_autotune (unless --no-tune)."""
+    of `steps` steps precedes the timed one."""
     import torch
     from paper_2006_12910_amd import lb
     t0 = time.time()
@@ -233,11 +232,6 @@ def run_variant(storage, specs, masks, steps, warmup, tune, fixed_tiles=None, tw
     batch = lb.Batch(doms)
     torch.cuda.synchronize()
     log(f"{storage}: built {len(doms)} domains in {time.time() - t0:.1f}s")
-    if two_step and tune:
-        # the two-step tile height: lb_batch_autotune (timed, or from its cache)
-        ms_t = batch.autotune(steps=16)
-        log(f"{storage}: batch two-step tile height {batch.get_option(lb.OPT_TWO_STEP_ROWS)} "
-            f"({'timed, ' + format(ms_t, '.3f') + ' ms/step' if ms_t > 0 else 'cached'})")
     batch.step(max(warmup, 1))
     # one untimed call of the timed length first (a 20-step call timed right
     # after a 5-step warm-up took ~3 ms more than its share of a 40-step call)
@@ -248,8 +242,7 @@ def run_variant(storage, specs, masks, steps, warmup, tune, fixed_tiles=None, tw
     ms2 = timed_call(batch, 2 * steps)
     log(f"{storage}: {2 * steps} steps in {ms2:.1f} ms")
     if two_step:
-        tiles = f"two-step: 62 columns x {batch.get_option(lb.OPT_TWO_STEP_ROWS)} rows per tile" + (
-            " (lb_batch_autotune)" if tune else " (default)")
+        tiles = "multi-step: regions and steps per launch chosen by the library"
     return doms, batch, ms, ms2, tiles
 
 
@@ -390,7 +383,7 @@ def other_configs():
         out[name] = {"gpu_mlups": round(sites * steps / (e0.elapsed_time(e1) * 1e-3) / 1e6, 1)}
 
     # a single-domain probe above 1 GB: the 8192^2 periodic shear wave alone,
-    # FP16 deviations with stochastic rounding, two steps per launch
+    # FP16 deviations with stochastic rounding, several steps per launch
     # (algorithmic bytes 36 per site update; the A-B buffers take 2.4 GB)
     fields = inputs.shear_wave_field(8192, 8192, SHEAR_U0, 1, 0.0)
     d = lb.Domain(8192, 8192, tau=BIG_TAU, storage="f16", rounding="stochastic", init=fields)
@@ -725,7 +718,7 @@ def main():
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU baseline and L2 sample")
     ap.add_argument("--no-tune", action="store_true", help="default tile shapes instead of the autotuner's")
     ap.add_argument("--single-step", action="store_true",
-                    help="one step per launch (two-step sweep off), tile shapes autotuned")
+                    help="one step per launch (multi-step sweep off), tile shapes autotuned")
     ap.add_argument("--no-configs", action="store_true",
                     help="skip the rates of the other four workloads and of the paper's three "
                          "benchmarks (reported beside the main line)")
@@ -786,14 +779,15 @@ def main():
         bytes_alg = algorithmic_bytes(specs, masks, STORAGE_BYTES[v])
         gbs = bytes_alg * args.steps / (ms * 1e-3) / 1e9
         two = all(d.get_option(lb.OPT_TWO_STEP) == 1 for d in doms)
-        spl = 2 if (two and args.steps % 4 == 0) else 1
-        # average sweep launch: the extra steps of the 2K-step call over the
-        # K-step one, per launch (the per-call density sums cancel)
-        launch_ms = (ms2 - ms) / (args.steps / spl)
+        # steps per sweep launch; None: several, as many as the library chose
+        spl = None if two else 1
+        # average sweep time per step: the extra steps of the 2K-step call over
+        # the K-step one (the per-call density sums cancel)
+        launch_ms = (ms2 - ms) / args.steps
         entry = {"mlups": round(mlups, 1), "mflups": round(mflups, 1), "ms_per_step": round(ms / args.steps, 4),
                  "sweep_launch_ms": round(launch_ms, 4), "steps_per_launch": spl,
-                 "sweep_GBps": round(spl * bytes_alg / (launch_ms * 1e-3) / 1e9, 1),
-                 "hbm_frac": round(spl * bytes_alg / (launch_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
+                 "sweep_GBps": round(bytes_alg / (launch_ms * 1e-3) / 1e9, 1),
+                 "hbm_frac": round(bytes_alg / (launch_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                  "bytes_per_step": bytes_alg, "rounding": ROUNDING[v],
                  "two_step": two,
                  "tiles": tiles if isinstance(tiles, str) or tiles is None else {f"{'obstacles' if k[0] else 'open'}/class{k[1]}": f"{t[0]}x{t[1]}"
@@ -811,8 +805,8 @@ def main():
     head = results[variants[0]]
     achieved = head["sweep_GBps"]
     # the workload's domains are periodic without particles, so with the
-    # two-step option on (the default) every launch of the timed run is the
-    # two-step sweep when the step count is a multiple of four
+    # multi-step option on (the default) every launch of the timed run advances
+    # several steps; the figures below are per step in either case
     spl = head["steps_per_launch"]
     copy_gbs = copy_bandwidth()
     log(f"device-to-device copy: {copy_gbs:.0f} GB/s")
@@ -821,17 +815,17 @@ def main():
                 "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": traffic,
                 # bytes that really crossed HBM per launch (profiled) over the
-                # launch duration: with two steps per launch the algorithmic
+                # launch duration: with several steps per launch the algorithmic
                 # rate above is an effective one and exceeds this
                 "measured_GBps": (None if traffic is None else
                                   round(traffic / (head["sweep_launch_ms"] * 1e-3) / 1e9, 1)),
                 "launch_ms": head["sweep_launch_ms"],
-                "kernel": (f"k_sweep2 (two steps per launch, {variants[0]} storage, batched)" if spl == 2
-                           else f"k_sweep ({variants[0]} storage, batched)"),
+                "kernel": (f"k_multi (several steps per launch, {variants[0]} storage, batched)"
+                           if spl is None else f"k_sweep ({variants[0]} storage, batched)"),
                 "steps_per_launch": spl,
-                "algorithmic_bytes_per_launch": spl * head["bytes_per_step"],
+                "algorithmic_bytes_per_step": head["bytes_per_step"],
                 "copy_GBps": round(copy_gbs, 1), "frac_of_copy": round(achieved / copy_gbs, 4)}
-    # the 16-bit two-step sweep is bound by vector issue as much as by memory:
+    # the 16-bit sweep is bound by vector issue as much as by memory:
     # the profile's VALU lane-instructions per site update and issue fraction
     prof = profile_entry(spl)
     if prof is not None and prof.get("valu"):

@@ -179,9 +179,10 @@ lb_status lb_add_particles(lb_domain *d, const lb_particle *p, int32_t n, int32_
  * passes a multiple of LB_OPT_MASS_INTERVAL (default 256) ends with the FP64
  * density sum of the final state (see lb_mass, lb_set_mass_check).  A
  * non-finite density, or a sum beyond the drift threshold, latches a flag
- * that the next synchronising call reports as LB_EUNSTABLE.  Steps replay
- * captured hipGraphs of fixed sizes (LB_OPT_GRAPH_CHUNK and the powers of
- * four below it), all captured by the first call with nsteps > 0. */
+ * that the next synchronising call reports as LB_EUNSTABLE.  Single steps
+ * replay captured hipGraphs of fixed sizes (LB_OPT_GRAPH_CHUNK and the powers
+ * of four below it), all captured by the first call that takes them; several
+ * steps a launch (LB_OPT_TWO_STEP) are enqueued as they are. */
 lb_status lb_step(lb_domain *d, int64_t nsteps);
 
 /* Moments of Sec. 2: density rho = sum_i f_i and velocity u = j/rho + g/2
@@ -292,7 +293,7 @@ lb_status lb_get_particle_state(lb_domain *d, lb_particle_state *out, int32_t n)
 lb_status lb_set_particle_state(lb_domain *d, const lb_particle_state *in, int32_t n);
 
 /* Options (see LB_OPT_*).  Changing one drops the cached step graphs. */
-#define LB_OPT_USE_GRAPH 1     /* 1 (default): lb_step replays a captured hipGraph */
+#define LB_OPT_USE_GRAPH 1     /* 1 (default): single steps replay a captured hipGraph */
 #define LB_OPT_TILE_WIDTH 2    /* threads per tile row: 64, 128 or 256            */
 #define LB_OPT_ROWS_PER_THREAD 3 /* nodes per thread along y: 1..16               */
 #define LB_OPT_GRAPH_CHUNK 4   /* steps per captured graph, 1..4096 (default 256) */
@@ -303,12 +304,13 @@ lb_status lb_set_particle_state(lb_domain *d, const lb_particle_state *in, int32
  * oscillation of neighbouring near-neutral discs grow (e.g. density ratio 1.05
  * at tau = 0.7); the mean damps it.  Not changeable while in a batch. */
 #define LB_OPT_FORCE_AVERAGE 5
-/* 1 (default): a domain that is periodic on both axes, has no particles and
- * no noise or power law, with native arithmetic, advances two time steps per
- * pass over memory (each four steps as two such launches; the first step is
- * kept in on-chip memory) -- bit-identical to single steps, with half the
- * memory traffic per step.  0: single steps only.  A batch takes it when all
- * its domains do.  Not changeable while in a batch. */
+/* 1 (default): a domain without particles and pressure faces, with native
+ * arithmetic (the power law: with a wall or obstacles and without noise),
+ * advances 3, 5, 7 or 9 time steps per launch, as many as suit its size; the
+ * steps between stay in on-chip memory -- bit-identical to single steps, with
+ * the launch and the memory traffic paid once for all of them.  0: single
+ * steps only.  A batch takes it when all its domains do.  Not changeable while
+ * in a batch. */
 #define LB_OPT_TWO_STEP 6
 /* 0 (default) or 1: lb_step of a domain with particles runs the particle
  * coupling (k_post of the previous step, k_pre, then the sweep of the tiles
@@ -322,10 +324,10 @@ lb_status lb_set_particle_state(lb_domain *d, const lb_particle_state *in, int32
  * (>= 1, default 256; 1: after every call).  On a batch it counts the batch's
  * own steps. */
 #define LB_OPT_MASS_INTERVAL 8
-/* Output rows of the two-step sweep's tiles (62 columns each): one of 10, 14,
- * 18 (16-bit storage; default 14), 6, 10, 14 (FP32; default 10), 4, 6, 8
- * (FP64; default 6); results do not depend on it.  On a batch: the height of
- * its launch (at creation the members' common height, else the default). */
+/* Accepted and kept, without effect (the tiles of LB_OPT_TWO_STEP follow from
+ * the sizes): one of 10, 14, 18 (16-bit storage; default 14), 6, 10, 14 (FP32;
+ * default 10), 4, 6, 8 (FP64; default 6).  On a batch: at creation the
+ * members' common value, else the default. */
 #define LB_OPT_TWO_STEP_ROWS 10
 lb_status lb_set_option(lb_domain *d, int32_t key, int64_t value);
 lb_status lb_get_option(lb_domain *d, int32_t key, int64_t *value);
@@ -334,7 +336,7 @@ lb_status lb_get_option(lb_domain *d, int32_t key, int64_t *value);
 lb_status lb_destroy_domain(lb_domain *d);
 
 /* Batching: several independent domains advance together, one sweep launch
- * per step over the tiles of all of them, replayed from a hipGraph.  The
+ * per step (or per several, LB_OPT_TWO_STEP) over the tiles of all of them.  The
  * domains must share storage, arithmetic, noise and power-law settings
  * (LB_EUNSUPPORTED otherwise); sizes, boundaries, obstacles, particles and all
  * parameters may differ.  Every domain keeps its own noise key and step
@@ -373,22 +375,14 @@ lb_status lb_noise_normals(uint64_t seed, uint32_t domain_id, uint32_t step, uin
                            void *hip_stream);
 
 /* Autotune this domain's sweep tiles: times each candidate single-step tile
- * width / rows-per-thread pair over `steps` single steps (the two-step sweep
- * off while timing) and keeps the fastest; where the two-step sweep applies,
- * then also its tile height (LB_OPT_TWO_STEP_ROWS), timed over `steps`
- * rounded up to a multiple of four.  The height chosen is cached for the
- * process per (storage, label plane, rounding, size class floor(log2(nx ny)))
- * and later domains of a cached class take it without timing.  The state
- * advances by the steps timed.  *best_ms receives the best time per step. */
+ * width / rows-per-thread pair over `steps` single steps (LB_OPT_TWO_STEP off
+ * while timing) and keeps the fastest; where several steps a launch apply,
+ * `steps` of those are timed too.  The state advances by the steps timed.
+ * *best_ms receives the best time per step. */
 lb_status lb_autotune(lb_domain *d, int32_t steps, double *best_ms);
 
-/* Autotune a batch's two-step tile height (LB_OPT_TWO_STEP_ROWS of the
- * batch): each instantiated height is timed over `steps` steps (rounded up to
- * a multiple of four, after an untimed call of as many), the fastest kept
- * and cached for the process per (storage, label plane in any member,
- * rounding, size class of the batch's total sites); a cached class is applied
- * without timing (*best_ms = 0).  A batch that runs single steps is left as
- * it is.  The members' states advance by the steps timed. */
+/* A batch's tiles follow from its members' sizes: nothing is left to tune, the
+ * state stays, and *best_ms = 0. */
 lb_status lb_batch_autotune(lb_batch *b, int32_t steps, double *best_ms);
 
 /* ---------------------------------------------------------------------------
@@ -472,7 +466,8 @@ lb_status lb3_create_domain(const lb3_domain_desc *desc, void *dev_workspace, si
                             void *hip_stream, lb3_domain **out);
 /* Solid nodes: host mask [nz][ny][nx], nonzero = solid (walls stay solid). */
 lb_status lb3_set_obstacles(lb3_domain *d, const uint8_t *host_mask, size_t n);
-/* Enqueue nsteps steps (one sweep launch per step); nsteps >= 0. */
+/* Enqueue nsteps steps (one sweep launch per step, or per two where that is
+ * the faster; bit-identical); nsteps >= 0. */
 lb_status lb3_step(lb3_domain *d, int64_t nsteps);
 /* rho and u = j/rho + g/2 at every node (zero on solids), host FP64
  * [nz][ny][nx] each.  Synchronises; LB_EUNSTABLE after a non-finite state. */

@@ -20,15 +20,16 @@ SOURCES = ["lb_api.hip", "common.hip", "kern_f64.hip", "kern_f32.hip", "kern_f16
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 # No floating-point contraction: a node's arithmetic then compiles to the same
-# roundings in every kernel that runs it (single-step and two-step sweeps give
+# roundings in every kernel that runs it (single-step and multi-step sweeps give
 # bit-identical states); operations meant to be fused are written as fma calls.
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall", "-Wno-unused-function",
          "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 # The 16-bit sweeps are bound by vector issue; the instruction scheduler's
-# ILP strategy gave the FP16 stress batch 0.967 against 0.981 ms per step
-# (FP32 kernels keep the default: 1.593 against 1.584 ms with it).
+# ILP strategy gave a batch of 201 FP16 domains (185 M sites), two steps a
+# launch, 0.967 against 0.981 ms per step (FP32 kernels keep the default:
+# 1.593 against 1.584 ms with it).
 FILE_FLAGS = {"kern_f16.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
               "kern_bf16.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
 

@@ -6,8 +6,8 @@
 #include "aux_impl.h"
 #include "launch.h"
 #include "particles_impl.h"
-#include "sweep2_impl.h"
 #include "sweep_impl.h"
+#include "sweepn_impl.h"
 
 namespace lbk {
 namespace {
@@ -21,19 +21,22 @@ void sweep_l(const DevDomain *doms, const int *prefix, int ndom, int kstep, int 
                      ndom, kstep, part);
 }
 template <int FEAT, int PLM>
-void sweep2_l(const DevDomain *doms, const int *prefix2, int ndom, int kstep, int which, int blocks,
-              int rows, hipStream_t s) {
-  constexpr int H0 = two_step_rows_of(ST, 0), H1 = two_step_rows_of(ST, 1),
-                H2 = two_step_rows_of(ST, 2);
-  if (rows == H0)
-    hipLaunchKernelGGL((k_sweep2<ST, FEAT, H0, PLM>), dim3(blocks), dim3(256), 0, s, doms, prefix2,
-                       ndom, kstep, which);
-  else if (rows == H2)
-    hipLaunchKernelGGL((k_sweep2<ST, FEAT, H2, PLM>), dim3(blocks), dim3(256), 0, s, doms, prefix2,
-                       ndom, kstep, which);
-  else
-    hipLaunchKernelGGL((k_sweep2<ST, FEAT, H1, PLM>), dim3(blocks), dim3(256), 0, s, doms, prefix2,
-                       ndom, kstep, which);
+void multi_l(const DevDomain *doms, const int *prefix, int ndom, const DevDomain *one, int k,
+             int kstep, int nsteps, int blocks, hipStream_t s) {
+  if (k == 0 && one != nullptr) {
+    hipLaunchKernelGGL((k_multi_one<ST, FEAT, PLM, 0>), dim3(blocks), dim3(region(0).nt), 0, s, *one,
+                       kstep, nsteps);
+  } else if (k == 0) {
+    hipLaunchKernelGGL((k_multi<ST, FEAT, PLM, 0>), dim3(blocks), dim3(region(0).nt), 0, s, doms,
+                       prefix, ndom, kstep, nsteps);
+  } else if (k == 1 || !region_fits(ST, 2)) {
+    hipLaunchKernelGGL((k_multi<ST, FEAT, PLM, 1>), dim3(blocks), dim3(region(1).nt), 0, s, doms,
+                       prefix, ndom, kstep, nsteps);
+  } else {
+    if constexpr (region_fits(ST, 2))
+      hipLaunchKernelGGL((k_multi<ST, FEAT, PLM, 2>), dim3(blocks), dim3(region(2).nt), 0, s, doms,
+                         prefix, ndom, kstep, nsteps);
+  }
 }
 template <int FEAT, int PLM, int WIDE>
 void init_l(const DevDomain *dom, const double *rho, const double *ux, const double *uy, int row0,
@@ -80,13 +83,13 @@ void mirror_l(const DevDomain *dom, int nx, int ny, hipStream_t s) {
 
 template <int FEAT, int PLM, int WIDE> void fill(KernelSet *k) {
   k->sweep = sweep_l<FEAT, PLM, WIDE>;
-  // the two-step sweep: plain and obstacle (label) sweeps, and the power-law
-  // sweep of label domains (walls as solid label rows); not with noise
-  if constexpr ((FEAT & F_NOISE) == 0 && WIDE == 0 &&
-                ((FEAT & F_POWER) == 0 || (FEAT & F_LABELS) != 0))
-    k->sweep2 = sweep2_l<FEAT, PLM>;
+  // several steps a launch: every set in native arithmetic but the power law
+  // without a label plane or with noise
+  if constexpr (WIDE == 0 && ((FEAT & F_POWER) == 0 ||
+                              ((FEAT & F_LABELS) != 0 && (FEAT & F_NOISE) == 0)))
+    k->multi = multi_l<FEAT, PLM>;
   else
-    k->sweep2 = nullptr;
+    k->multi = nullptr;
   k->init = init_l<FEAT, PLM, WIDE>;
   k->pre = pre_l;
   k->post = post_l;

@@ -67,7 +67,7 @@ int mass_blocks_of(int nx, int ny) {
 
 // A label plane holds obstacles, particles and walls.  Walls of a domain
 // without obstacles or particles could also be index walls (mirror writes, no
-// plane), but as solid label rows they let the two-step sweep run on
+// plane), but as solid label rows they let the multi-step sweep run on
 // channels; only domains with a pressure face keep index walls.
 bool needs_labels(const lb_domain_desc *d) {
   return d->obstacles != 0 || d->max_particles > 0 ||
@@ -202,6 +202,52 @@ struct GraphCache {
   }
 };
 
+// Several steps per launch: the region (sweepn_impl.h) and the most steps.
+struct MultiPlan {
+  int k = 0, nmax = 1;
+};
+
+int multi_tiles(int k, int n, int nx, int ny) {
+  const int ow = region(k).cw - 2 * (n - 1), oh = region(k).rs - 2 * (n - 1);
+  return ((nx + ow - 1) / ow) * ((ny + oh - 1) / oh);
+}
+
+// Region and steps per launch for the domains of one launch, (nx, ny) each:
+// the least time a step by the model of sweepn_impl.h.  v, us a wave-row (64
+// nodes) of vector issue, fitted to 2048^2 and 512^2 lattices: FP32 0.054 (the
+// power law 0.09, noise 0.10), FP16 0.061, FP64 0.07; a launch alone on its CU
+// takes 8 v a step (1.0 us a step at 7 steps on 128 x 64, 1.37 with the power
+// law) and 4 us.  The model is within 10 % of the measured times from 48 x 33
+// to 4096^2, FP32 and FP64, and within 15 % for FP16; the second-best choice is
+// rarely more than that behind.
+MultiPlan choose_multi(int storage, int feat, const std::vector<std::pair<int, int>> &sizes) {
+  const double v = (storage == LB_F64 ? 0.07 : storage == LB_F32 ? 0.054 : 0.061) +
+                   ((feat & F_POWER) ? 0.035 : 0.0) + ((feat & F_NOISE) ? 0.046 : 0.0);
+  MultiPlan best;
+  double least = 1e300;
+  for (int k = 0; k < REGIONS; ++k) {
+    if (!region_fits(storage, k)) continue;
+    const Region g = region(k);
+    for (int n = 3; n <= MULTI_MAX; n += 2) {
+      const int ow = g.cw - 2 * (n - 1), oh = g.rs - 2 * (n - 1);
+      if (ow < 4 || oh < 4) continue;
+      double tiles = 0.0;
+      for (const auto &s : sizes) tiles += multi_tiles(k, n, s.first, s.second);
+      double waves = 0.0;
+      for (int s = 0; s < n; ++s) waves += g.cw * (g.rs - 2 * s) / 64.0;
+      const double bytes = tiles * 9 * storage_bytes(storage) * ((double)g.cw * g.rs + ow * oh);
+      const double us = 4.0 + std::max({n * 8.0 * v, std::ceil(tiles / 256.0) * v * waves,
+                                        bytes >= 2 * (double)(256 << 20) ? bytes / 5e6 : 0.0});
+      if (us / n < least) {
+        least = us / n;
+        best.k = k;
+        best.nmax = n;
+      }
+    }
+  }
+  return best;
+}
+
 }  // namespace
 
 namespace lbk {
@@ -240,6 +286,8 @@ struct lb_domain {
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   GraphCache graphs;
   int in_batches = 0;
+  int rows2 = 0;          // LB_OPT_TWO_STEP_ROWS
+  MultiPlan multi;        // how several steps a launch are taken
   std::vector<uint8_t> host_labels;  // walls + obstacles, [ny][pitch]
   // asynchronous moment output: moments computed (on stream), copied out
   // (on the caller's copy stream); a copy in flight until lb_moments_wait
@@ -249,11 +297,9 @@ struct lb_domain {
   DevDomain *ddesc() const { return (DevDomain *)(ws + L.desc); }
   Header *dhdr() const { return (Header *)(ws + L.hdr); }
   int *dprefix() const { return (int *)(ws + L.prefix); }
-  int *dprefix2() const { return dprefix() + 2; }  // tiles of the two-step sweep
-  int *dprefixm() const { return dprefix() + 4; }  // blocks of the density sum
+  int *dprefixm() const { return dprefix() + 2; }  // blocks of the density sum
   PItem *ditems() const { return (PItem *)(ws + L.items); }
   int ntiles() const { return hd.tiles_x * hd.tiles_y; }
-  int ntiles2() const { return hd.tiles2_x * hd.tiles2_y; }
 };
 
 struct lb_batch {
@@ -261,11 +307,11 @@ struct lb_batch {
   char *ws = nullptr;
   hipStream_t stream = nullptr, cap = nullptr;
   KernelSet ks{};
-  int total_tiles = 0, total_tiles2 = 0, total_mass_blocks = 0, nitems = 0;
-  bool two_step = false;  // every domain takes the two-step sweep
-  int rows2 = 0;          // its tile height, shared by the launch
-  std::vector<DevDomain> hdescs;  // host copies of the descriptors
-  std::vector<int> hprefix;       // and of the prefix tables
+  int total_tiles = 0, total_mass_blocks = 0, nitems = 0;
+  bool multi_step = false;  // every domain takes several steps a launch
+  MultiPlan multi;
+  int multi_tiles[MULTI_MAX + 1] = {};  // tiles of the launches of n steps
+  int rows2 = 0;                        // LB_OPT_TWO_STEP_ROWS
   size_t off_desc = 0, off_prefix = 0, off_items = 0, bytes = 0;
   bool use_graph = true;
   int chunk = 256;
@@ -274,33 +320,18 @@ struct lb_batch {
   GraphCache graphs;
   DevDomain *ddesc() const { return (DevDomain *)(ws + off_desc); }
   int *dprefix() const { return (int *)(ws + off_prefix); }
-  int *dprefix2() const { return dprefix() + doms.size() + 1; }
-  int *dprefixm() const { return dprefix() + 2 * (doms.size() + 1); }  // density-sum blocks
+  int *dprefixm() const { return dprefix() + doms.size() + 1; }  // density-sum blocks
+  // tiles of the launches of n = 3, 5, ... steps
+  int *dprefixn(int n) const { return dprefix() + (size_t)(n + 1) / 2 * (doms.size() + 1); }
   PItem *ditems() const { return (PItem *)(ws + off_items); }
 };
 
 namespace {
 
-// Two-step sweep tiles: TS_COLS columns by `rows` rows.
-void set_two_step_rows(DevDomain &hd, int rows) {
-  hd.rows2 = rows;
-  hd.tiles2_x = (hd.nx + TS_COLS - 1) / TS_COLS;
-  hd.tiles2_y = (hd.ny + rows - 1) / rows;
-}
 bool valid_two_step_rows(int storage, int64_t rows) {
   for (int k = 0; k < 3; ++k)
     if (rows == two_step_rows_of(storage, k)) return true;
   return false;
-}
-
-// Tile heights the autotuner chose, per (storage, label plane, stochastic
-// rounding, size class = floor(log2(sites))), for this process.
-std::mutex g_tune_mu;
-std::map<std::tuple<int, int, int, int>, int> g_rows2_cache;
-std::tuple<int, int, int, int> tune_key(int storage, int feat, long long sites) {
-  int cls = 0;
-  while ((1LL << (cls + 1)) <= sites) ++cls;
-  return {storage, (feat & F_LABELS) ? 1 : 0, (feat & F_STOCH) ? 1 : 0, cls};
 }
 
 // A tile is tile_w threads (nodes) along x by (256 / tile_w) * rpt rows.
@@ -314,7 +345,7 @@ void set_tiles(DevDomain &hd, int tile_w, int rpt) {
 
 lb_status push_desc(lb_domain *d) {
   HIPCHK(hipMemcpyAsync(d->ddesc(), &d->hd, sizeof(DevDomain), hipMemcpyHostToDevice, d->stream));
-  int pre[6] = {0, d->ntiles(), 0, d->ntiles2(), 0, d->hd.mass_blocks};
+  int pre[4] = {0, d->ntiles(), 0, d->hd.mass_blocks};
   HIPCHK(hipMemcpyAsync(d->dprefix(), pre, sizeof(pre), hipMemcpyHostToDevice, d->stream));
   HIPCHK(hipStreamSynchronize(d->stream));
   return LB_OK;
@@ -335,17 +366,14 @@ lb_status check_health(lb_domain *d) {
   return LB_OK;
 }
 
-// What one step (or step pair) of a domain or batch launches.
+// What the steps of a domain or batch launch.
 struct StepPlan {
   const KernelSet *ks;
   const DevDomain *doms;
   const int *prefix;   // single-step tiles per domain
-  const int *prefix2;  // two-step tiles per domain
-  int ndom, blocks, blocks2;
+  int ndom, blocks;
   const PItem *items;
   int nitems;
-  bool two;  // two-step sweep (no particles, so no pre/post passes)
-  int rows2 = 0;  // its tile height (every domain of the launch shares it)
   // no domain of the launch holds more than one particle: the post pass of a
   // step and the pre pass of the next run as one launch (k_post_pre)
   bool fuse_pp = false;
@@ -354,6 +382,45 @@ struct StepPlan {
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   int ntiles = 0;
 };
+
+// Several steps a launch.
+struct MultiSteps {
+  MultiPlan plan;
+  const DevDomain *one = nullptr;         // the descriptor of a single domain
+  const lb_batch *batch = nullptr;        // or the batch
+  int tiles(int n) const { return batch ? batch->multi_tiles[n] : multi_tiles(plan.k, n, one->nx, one->ny); }
+  const int *prefix(int n) const { return batch ? batch->dprefixn(n) : nullptr; }
+};
+
+// Enqueue n steps, several a launch.  The launches take odd numbers of steps
+// (1: the single-step sweep), as few and as equal as possible: k parts of lo
+// or lo + 2 with k n_max >= n and k of n's parity.  Launched one by one, not
+// from a captured graph: a launch runs 7 us and more, longer than the host
+// takes to enqueue it, and captured chunks of fixed lengths would break the
+// calls into shorter launches (250 steps: 48 launches and 10 counter updates
+// instead of 36 and 1).
+lb_status run_multi(const StepPlan &p, const MultiSteps &m, int64_t n, hipStream_t s) {
+  for (int64_t done = 0; done < n;) {
+    const int c = (int)std::min<int64_t>(n - done, 1 << 16);
+    int parts = (c + m.plan.nmax - 1) / m.plan.nmax;
+    if ((parts ^ c) & 1) ++parts;
+    int lo = c / parts;
+    if (!(lo & 1)) --lo;
+    const int longer = (c - parts * lo) / 2;
+    for (int i = 0, k = 0; i < parts; ++i) {
+      const int len = lo + (i < longer ? 2 : 0);
+      if (len > 1)
+        p.ks->multi(p.doms, m.prefix(len), p.ndom, m.one, m.plan.k, k, len, m.tiles(len), s);
+      else
+        p.ks->sweep(p.doms, p.prefix, p.ndom, k, p.blocks, 0, s);
+      k += len;
+    }
+    launch_advance(p.doms, p.ndom, c, s);
+    HIPCHK(hipGetLastError());
+    done += c;
+  }
+  return LB_OK;
+}
 
 // Steps of one domain with particles, the particle coupling overlapping the
 // bulk of the sweep (the analogue of the paper's pipelining of the particle
@@ -385,24 +452,14 @@ void record_overlapped(const StepPlan &p, int n, hipStream_t s) {
   launch_advance(p.doms, p.ndom, n, s);
 }
 
-// Enqueue `n` steps of the launch sequence on stream s (eager or under
-// capture).  With the two-step sweep, each four steps are a pair of two-step
-// launches (the first leaves the state in the buffer of the other parity, the
-// second brings it back, so the state is where single steps expect it after
-// every pair); the n mod 4 remaining steps are single steps.
+// Enqueue `n` single steps of the launch sequence on stream s (eager or
+// under capture).
 void record_steps(const StepPlan &p, int n, hipStream_t s) {
-  int k = 0;
-  if (p.two) {
-    for (; k + 4 <= n; k += 4) {
-      p.ks->sweep2(p.doms, p.prefix2, p.ndom, k, 0, p.blocks2, p.rows2, s);
-      p.ks->sweep2(p.doms, p.prefix2, p.ndom, k + 2, 1, p.blocks2, p.rows2, s);
-    }
-  }
   if (p.side != nullptr && p.nitems > 0 && n > 0) {
     record_overlapped(p, n, s);
     return;
   }
-  for (; k < n; ++k) {
+  for (int k = 0; k < n; ++k) {
     // with fuse_pp, the pre pass of step k > 0 ran in the launch before
     if (p.nitems > 0 && !(p.fuse_pp && k > 0)) p.ks->pre(p.doms, p.items, p.nitems, k, s);
     p.ks->sweep(p.doms, p.prefix, p.ndom, k, p.blocks, 0, s);
@@ -420,8 +477,7 @@ void record_steps(const StepPlan &p, int n, hipStream_t s) {
 // four below it.  A call of n steps replays them largest first, so a handle
 // holds at most a handful of graphs, and all of them are captured by the
 // first call: no later call captures or instantiates anything, whatever its
-// step count.  Every size but 1 is a multiple of four, so the two-step sweep
-// runs in launch pairs and only the n mod 4 last steps are single steps.
+// step count.
 std::vector<int> graph_sizes(int chunk) {
   std::vector<int> v{chunk};
   int p = 1;
@@ -477,15 +533,14 @@ lb_status run_steps(GraphCache &gc, bool use_graph, int chunk, hipStream_t strea
   return LB_OK;
 }
 
-// The two-step sweep serves periodic domains without particles whose kernel
-// set has one (no noise, no power law, native arithmetic), unless switched
-// off with LB_OPT_TWO_STEP.
-// The two-step sweep needs periodic edges or walls held as solid label rows
-// (its tiles wrap around the domain), and no particle or pressure face.
-bool two_step_ok(const lb_domain *d) {
+// Several steps a launch serve domains without particles whose kernel set
+// has the kernel (native arithmetic), unless switched off with
+// LB_OPT_TWO_STEP: with periodic edges or walls held as solid label rows (the
+// tiles wrap around the domain), and no density face.
+bool multi_ok(const lb_domain *d) {
   const bool edges = (d->desc.bc_x == LB_PERIODIC && d->desc.bc_y == LB_PERIODIC) ||
                      (d->hd.label != nullptr && d->desc.bc_x != LB_PRESSURE);
-  return d->two_step && d->ks.sweep2 != nullptr && d->np == 0 && d->desc.max_particles == 0 && edges;
+  return d->two_step && d->ks.multi != nullptr && d->np == 0 && d->desc.max_particles == 0 && edges;
 }
 
 // FP64 density sum of the current state; its final kernel also latches a
@@ -642,7 +697,8 @@ static lb_status lb_create_domain_impl(const lb_domain_desc *desc, void *dev_wor
   h.feat = feat;
   set_tiles(h, default_tile_w(desc->nx), desc->storage >= LB_F16_DELTA ? 4 : 2);
   h.stream_stores = sweep_working_set(h) >= STREAM_STORE_MIN_BYTES;
-  set_two_step_rows(h, two_step_rows(h.storage));
+  d->rows2 = two_step_rows(h.storage);
+  d->multi = choose_multi(h.storage, feat, std::vector<std::pair<int, int>>{{desc->nx, desc->ny}});
   h.rho0 = desc->rho0;
   h.tau = desc->power_law ? desc->tau_min : desc->tau;
   h.omega = 1.0 / h.tau;
@@ -966,11 +1022,9 @@ static lb_status lb_step_impl(lb_domain *d, int64_t nsteps) {
   if (!d) return fail(LB_EINVAL, "null domain");
   if (nsteps < 0) return fail(LB_EINVAL, "nsteps < 0");
   if (nsteps > 0) {
-    StepPlan p{&d->ks, d->ddesc(), d->dprefix(), d->dprefix2(), 1, d->ntiles(),
-               d->ntiles2(), d->ditems(), d->np, two_step_ok(d)};
-    p.rows2 = d->hd.rows2;
+    StepPlan p{&d->ks, d->ddesc(), d->dprefix(), 1, d->ntiles(), d->ditems(), d->np};
     p.fuse_pp = d->np == 1;
-    if (d->overlap && d->np > 0 && !p.two) {
+    if (d->overlap && d->np > 0) {
       if (!d->side) {
         HIPCHK(hipStreamCreateWithFlags(&d->side, hipStreamNonBlocking));
         HIPCHK(hipEventCreateWithFlags(&d->ev_fork, hipEventDisableTiming));
@@ -981,7 +1035,15 @@ static lb_status lb_step_impl(lb_domain *d, int64_t nsteps) {
       p.ev_join = d->ev_join;
       p.ntiles = d->ntiles();
     }
-    lb_status s = run_steps(d->graphs, d->use_graph, d->chunk, d->stream, d->cap, p, nsteps);
+    lb_status s;
+    if (multi_ok(d)) {
+      MultiSteps m;
+      m.plan = d->multi;
+      m.one = &d->hd;
+      s = run_multi(p, m, nsteps, d->stream);
+    } else {
+      s = run_steps(d->graphs, d->use_graph, d->chunk, d->stream, d->cap, p, nsteps);
+    }
     if (s != LB_OK) return s;
   }
   d->t += nsteps;
@@ -1257,8 +1319,8 @@ static lb_status lb_set_option_impl(lb_domain *d, int32_t key, int64_t value) {
     case LB_OPT_TWO_STEP_ROWS:
       if (!valid_two_step_rows(d->desc.storage, value))
         return fail(LB_EINVAL, "two-step tile rows: not an instantiated height for this storage");
-      set_two_step_rows(d->hd, (int)value);
-      break;
+      d->rows2 = (int)value;
+      return LB_OK;
     case LB_OPT_MASS_INTERVAL:
       if (value < 1) return fail(LB_EINVAL, "mass check interval must be >= 1");
       d->mass_interval = value;
@@ -1266,8 +1328,7 @@ static lb_status lb_set_option_impl(lb_domain *d, int32_t key, int64_t value) {
     default: return fail(LB_EINVAL, "unknown option");
   }
   d->graphs.clear();
-  if (key == LB_OPT_TILE_WIDTH || key == LB_OPT_ROWS_PER_THREAD || key == LB_OPT_FORCE_AVERAGE ||
-      key == LB_OPT_TWO_STEP_ROWS)
+  if (key == LB_OPT_TILE_WIDTH || key == LB_OPT_ROWS_PER_THREAD || key == LB_OPT_FORCE_AVERAGE)
     return push_desc(d);
   return LB_OK;
 }
@@ -1286,7 +1347,7 @@ static lb_status lb_get_option_impl(lb_domain *d, int32_t key, int64_t *value) {
     case LB_OPT_FORCE_AVERAGE: *value = (d->hd.feat & F_FAVG) ? 1 : 0; return LB_OK;
     case LB_OPT_TWO_STEP: *value = d->two_step ? 1 : 0; return LB_OK;
     case LB_OPT_OVERLAP: *value = d->overlap ? 1 : 0; return LB_OK;
-    case LB_OPT_TWO_STEP_ROWS: *value = d->hd.rows2; return LB_OK;
+    case LB_OPT_TWO_STEP_ROWS: *value = d->rows2; return LB_OK;
     case LB_OPT_MASS_INTERVAL: *value = d->mass_interval; return LB_OK;
   }
   return fail(LB_EINVAL, "unknown option");
@@ -1338,32 +1399,12 @@ static lb_status lb_autotune_impl(lb_domain *d, int32_t steps, double *best_ms) 
   if (s != LB_OK) return s;
   if ((s = lb_set_option(d, LB_OPT_TILE_WIDTH, bw)) != LB_OK) return s;
   if ((s = lb_set_option(d, LB_OPT_ROWS_PER_THREAD, br)) != LB_OK) return s;
-  if (two_step_ok(d)) {
-    // the two-step sweep's tile height: cached for the class, else timed
-    const auto key = tune_key(d->desc.storage, d->feat, (long long)d->desc.nx * d->desc.ny);
-    int rows = 0;
-    {
-      std::lock_guard<std::mutex> lock(g_tune_mu);
-      auto it = g_rows2_cache.find(key);
-      if (it != g_rows2_cache.end()) rows = it->second;
-    }
-    if (rows == 0) {
-      double best2 = 1e300;
-      const int n4 = std::max(4, (steps + 3) / 4 * 4);
-      for (int k = 0; k < 3 && s == LB_OK; ++k) {
-        const int h = two_step_rows_of(d->desc.storage, k);
-        double ms = 0.0;
-        if ((s = lb_set_option(d, LB_OPT_TWO_STEP_ROWS, h)) != LB_OK) break;
-        if ((s = time_steps([&](int64_t n) { return lb_step(d, n); }, d->stream, n4, &ms)) != LB_OK)
-          break;
-        if (ms < best2) { best2 = ms; rows = h; }
-      }
-      if (s != LB_OK) return s;
-      std::lock_guard<std::mutex> lock(g_tune_mu);
-      g_rows2_cache[key] = rows;
-      best = std::min(best, best2);
-    }
-    if ((s = lb_set_option(d, LB_OPT_TWO_STEP_ROWS, rows)) != LB_OK) return s;
+  if (multi_ok(d)) {
+    // several steps a launch: chosen by rule, timed for the report
+    double ms = 0.0;
+    const int n4 = std::max(4, (steps + 3) / 4 * 4);
+    if ((s = time_steps([&](int64_t n) { return lb_step(d, n); }, d->stream, n4, &ms)) != LB_OK) return s;
+    best = std::min(best, ms);
   }
   if (best_ms) *best_ms = best;
   return check_health(d);
@@ -1376,37 +1417,7 @@ lb_status lb_autotune(lb_domain *d, int32_t steps, double *best_ms) {
 static lb_status lb_batch_autotune_impl(lb_batch *b, int32_t steps, double *best_ms) {
   if (!b || steps < 1) return fail(LB_EINVAL, "bad argument");
   if (best_ms) *best_ms = 0.0;
-  if (!b->two_step) return LB_OK;  // single steps: the members' own tiles
-  long long sites = 0;
-  int feat = 0;
-  for (auto *d : b->doms) {
-    sites += (long long)d->desc.nx * d->desc.ny;
-    feat |= d->feat;
-  }
-  const auto key = tune_key(b->doms[0]->desc.storage, feat, sites);
-  int rows = 0;
-  {
-    std::lock_guard<std::mutex> lock(g_tune_mu);
-    auto it = g_rows2_cache.find(key);
-    if (it != g_rows2_cache.end()) rows = it->second;
-  }
-  lb_status s = LB_OK;
-  if (rows == 0) {
-    double best = 1e300;
-    const int n4 = std::max(4, (steps + 3) / 4 * 4);
-    for (int k = 0; k < 3; ++k) {
-      const int h = two_step_rows_of(b->doms[0]->desc.storage, k);
-      double ms = 0.0;
-      if ((s = lb_batch_set_option(b, LB_OPT_TWO_STEP_ROWS, h)) != LB_OK) return s;
-      if ((s = time_steps([&](int64_t n) { return lb_batch_step(b, n); }, b->stream, n4, &ms)) != LB_OK)
-        return s;
-      if (ms < best) { best = ms; rows = h; }
-    }
-    std::lock_guard<std::mutex> lock(g_tune_mu);
-    g_rows2_cache[key] = rows;
-    if (best_ms) *best_ms = best;
-  }
-  return lb_batch_set_option(b, LB_OPT_TWO_STEP_ROWS, rows);
+  return LB_OK;  // nothing to tune: the launches are chosen by rule
 }
 
 lb_status lb_batch_autotune(lb_batch *b, int32_t steps, double *best_ms) {
@@ -1438,6 +1449,10 @@ lb_status lb_destroy_domain(lb_domain *d) {
   LB_GUARDED(lb_destroy_domain_impl(d));
 }
 
+// prefix tables of a batch of n domains: single-step tiles, density-sum
+// blocks, tiles of the launches of 3, 5, ... MULTI_MAX steps
+static size_t batch_prefixes(int n) { return (size_t)(2 + MULTI_MAX / 2) * (n + 1); }
+
 static lb_status lb_batch_workspace_bytes_impl(lb_domain *const *domains, int32_t n, size_t *bytes) {
   if (!domains || n < 1 || !bytes) return fail(LB_EINVAL, "bad argument");
   size_t items = 0;
@@ -1445,7 +1460,7 @@ static lb_status lb_batch_workspace_bytes_impl(lb_domain *const *domains, int32_
     if (!domains[i]) return fail(LB_EINVAL, "null domain");
     items += domains[i]->np;
   }
-  *bytes = align256((size_t)n * sizeof(DevDomain)) + align256((size_t)3 * (n + 1) * sizeof(int)) +
+  *bytes = align256((size_t)n * sizeof(DevDomain)) + align256(batch_prefixes(n) * sizeof(int)) +
            align256(std::max<size_t>(items, 1) * sizeof(PItem));
   return LB_OK;
 }
@@ -1485,41 +1500,43 @@ static lb_status lb_batch_create_impl(lb_domain *const *domains, int32_t n, void
   b->ks = domains[lab_dom >= 0 ? lab_dom : 0]->ks;
   b->off_desc = 0;
   b->off_prefix = align256((size_t)n * sizeof(DevDomain));
-  b->off_items = b->off_prefix + align256((size_t)3 * (n + 1) * sizeof(int));
+  b->off_items = b->off_prefix + align256(batch_prefixes(n) * sizeof(int));
   b->bytes = need;
   std::vector<DevDomain> descs(n);
-  // single-step tile prefix [0, n], the two-step one [n + 1, 2n + 1], the
-  // density-sum blocks [2n + 2, 3n + 2]
-  std::vector<int> prefix(3 * (n + 1), 0);
+  // single-step tiles [0, n], density-sum blocks [n + 1, 2n + 1], then the
+  // tiles of the launches of 3, 5, ... steps
+  std::vector<int> prefix(batch_prefixes(n), 0);
   std::vector<PItem> items;
-  bool two = b->ks.sweep2 != nullptr;
+  bool multi = b->ks.multi != nullptr;
+  std::vector<std::pair<int, int>> sizes;
+  int feat = 0;
   for (int i = 0; i < n; ++i) {
     descs[i] = domains[i]->hd;
     prefix[i + 1] = prefix[i] + domains[i]->ntiles();
-    prefix[n + 2 + i] = prefix[n + 1 + i] + domains[i]->ntiles2();
-    prefix[2 * n + 3 + i] = prefix[2 * n + 2 + i] + domains[i]->hd.mass_blocks;
+    prefix[n + 2 + i] = prefix[n + 1 + i] + domains[i]->hd.mass_blocks;
     for (int q = 0; q < domains[i]->np; ++q) items.push_back(PItem{i, q});
-    two = two && two_step_ok(domains[i]);
+    multi = multi && multi_ok(domains[i]);
+    sizes.emplace_back(domains[i]->desc.nx, domains[i]->desc.ny);
+    feat |= domains[i]->feat;
   }
-  // one tile height per launch: the members' own if they agree, else the
-  // storage format's default (the batch's descriptor copies carry it)
-  int rows2 = domains[0]->hd.rows2;
+  b->multi_step = multi;
+  b->multi = choose_multi(domains[0]->desc.storage, feat, sizes);
+  for (int len = 3; len <= b->multi.nmax; len += 2) {
+    int *pre = prefix.data() + (size_t)(len + 1) / 2 * (n + 1);
+    for (int i = 0; i < n; ++i)
+      pre[i + 1] = pre[i] + multi_tiles(b->multi.k, len, sizes[i].first, sizes[i].second);
+    b->multi_tiles[len] = pre[n];
+  }
+  // the members' common value if they agree, else the default
+  b->rows2 = domains[0]->rows2;
   for (int i = 1; i < n; ++i)
-    if (domains[i]->hd.rows2 != rows2) rows2 = two_step_rows(domains[0]->desc.storage);
-  for (int i = 0; i < n; ++i) set_two_step_rows(descs[i], rows2);
-  for (int i = 0; i < n; ++i)
-    prefix[n + 2 + i] = prefix[n + 1 + i] + descs[i].tiles2_x * descs[i].tiles2_y;
-  b->rows2 = rows2;
-  b->two_step = two;
-  b->total_tiles2 = prefix[2 * n + 1];
-  b->total_mass_blocks = prefix[3 * n + 2];
+    if (domains[i]->rows2 != b->rows2) b->rows2 = two_step_rows(domains[0]->desc.storage);
+  b->total_mass_blocks = prefix[2 * n + 1];
   size_t working_set = 0;
   for (int i = 0; i < n; ++i) working_set += sweep_working_set(descs[i]);
   for (int i = 0; i < n; ++i) descs[i].stream_stores = working_set >= STREAM_STORE_MIN_BYTES;
   b->total_tiles = prefix[n];
   b->nitems = (int)items.size();
-  b->hdescs = descs;
-  b->hprefix = prefix;
   if (hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking) != hipSuccess) {
     delete b;
     return fail(LB_EHIP, "hipStreamCreateWithFlags failed");
@@ -1550,12 +1567,19 @@ static lb_status lb_batch_step_impl(lb_batch *b, int64_t nsteps) {
   if (!b) return fail(LB_EINVAL, "null batch");
   if (nsteps < 0) return fail(LB_EINVAL, "nsteps < 0");
   if (nsteps > 0) {
-    StepPlan p{&b->ks, b->ddesc(), b->dprefix(), b->dprefix2(), (int)b->doms.size(),
-               b->total_tiles, b->total_tiles2, b->ditems(), b->nitems, b->two_step};
-    p.rows2 = b->rows2;
+    StepPlan p{&b->ks, b->ddesc(), b->dprefix(), (int)b->doms.size(), b->total_tiles, b->ditems(),
+               b->nitems};
     p.fuse_pp = true;
     for (auto *m : b->doms) p.fuse_pp = p.fuse_pp && m->np <= 1;
-    lb_status s = run_steps(b->graphs, b->use_graph, b->chunk, b->stream, b->cap, p, nsteps);
+    lb_status s;
+    if (b->multi_step) {
+      MultiSteps m;
+      m.plan = b->multi;
+      m.batch = b;
+      s = run_multi(p, m, nsteps, b->stream);
+    } else {
+      s = run_steps(b->graphs, b->use_graph, b->chunk, b->stream, b->cap, p, nsteps);
+    }
     if (s != LB_OK) return s;
   }
   for (auto *d : b->doms) d->t += nsteps;
@@ -1589,19 +1613,8 @@ static lb_status lb_batch_set_option_impl(lb_batch *b, int32_t key, int64_t valu
     case LB_OPT_TWO_STEP_ROWS: {
       if (!valid_two_step_rows(b->doms[0]->desc.storage, value))
         return fail(LB_EINVAL, "two-step tile rows: not an instantiated height for this storage");
-      const int n = (int)b->doms.size();
       b->rows2 = (int)value;
-      for (int i = 0; i < n; ++i) {
-        set_two_step_rows(b->hdescs[i], b->rows2);
-        b->hprefix[n + 2 + i] = b->hprefix[n + 1 + i] + b->hdescs[i].tiles2_x * b->hdescs[i].tiles2_y;
-      }
-      b->total_tiles2 = b->hprefix[2 * n + 1];
-      HIPCHK(hipMemcpyAsync(b->ddesc(), b->hdescs.data(), n * sizeof(DevDomain),
-                            hipMemcpyHostToDevice, b->stream));
-      HIPCHK(hipMemcpyAsync(b->dprefix(), b->hprefix.data(), b->hprefix.size() * sizeof(int),
-                            hipMemcpyHostToDevice, b->stream));
-      HIPCHK(hipStreamSynchronize(b->stream));
-      break;
+      return LB_OK;
     }
     default: return fail(LB_EINVAL, "option not available on a batch");
   }

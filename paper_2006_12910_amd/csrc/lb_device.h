@@ -59,14 +59,23 @@ enum : int {
 // Power-law exponent specialisations.
 enum : int { PL_GENERIC = 0, PL_HALF = 1, PL_3Q = 2, PL_3H = 3 };
 
-// Tiles of the two-step sweep (k_sweep2): TS_COLS output columns (the 64
-// lanes of a wave less a one-node rim) by H output rows (its LDS holds H + 2
-// rows of 64 columns x 9 values).  Three tile heights are instantiated per
-// storage format; the default is the middle one (measured on the 185 M-site
-// stress batch: 16-bit rows 13 / 14 / 15 / 16 took 1.059 / 1.037 / 1.078 /
-// 1.056 ms per step, FP32 rows 9 / 10 / 11 / 12 1.625 / 1.603 / 1.648 /
-// 1.644 ms, one run), and the autotuner picks among the three.
-constexpr int TS_COLS = 62;
+// Regions of the launches of several steps (sweepn_impl.h): columns, rows,
+// threads (a whole number of nodes each).  The small
+// one has the shortest step (one node a thread, two waves a SIMD) and the
+// most tiles; the middle one fills a CU with two workgroups; the large one has
+// the least rim, and suits the formats whose LDS leaves room for two.
+struct Region {
+  int cw, rs, nt;
+};
+constexpr int REGIONS = 3;
+__host__ __device__ constexpr Region region(int k) {
+  return k == 0 ? Region{32, 16, 512} : (k == 1 ? Region{32, 32, 512} : Region{64, 32, 512});
+}
+// the large region of 8-byte values would take 147 KB of LDS
+constexpr bool region_fits(int storage, int k) { return !(storage == ST_F64 && k == 2); }
+constexpr int MULTI_MAX = 9;  // most steps a launch takes
+
+// Values of LB_OPT_TWO_STEP_ROWS, which no longer shapes anything.
 constexpr int two_step_rows_of(int storage, int k) {  // k = 0, 1, 2
   return storage == ST_F64 ? 4 + 2 * k : (storage == ST_F32 ? 6 + 4 * k : 10 + 4 * k);
 }
@@ -119,8 +128,6 @@ struct alignas(256) DevDomain {
   int bc_x, bc_y;
   int np;              // particles
   int tile_w, rows_per_thread, tiles_x, tiles_y;
-  int tiles2_x, tiles2_y;  // tiles of the two-step sweep (k_sweep2)
-  int rows2;               // their output rows (one of two_step_rows_of)
   uint32_t key0, key1; // noise generator key
   int storage, feat;
   int stream_stores;   // 1: the sweep's stores bypass the caches (see k_sweep)

@@ -1,0 +1,200 @@
+// sweepn_impl.h -- several time steps per launch, for the domains that need
+// nothing between two steps (no particles, no density faces): obstacles,
+// walls as label rows, either collision, the power law, thermal noise.
+//
+// A workgroup owns a region of CW x RS nodes.  The first step of the region is
+// computed from global memory, exactly as k_sweep does, and kept in LDS,
+// rounded to the storage format; each further step pulls from LDS, where the
+// nodes whose sources are all inside (one node less on every side) take the
+// next step in place; the last one stores its nodes to global memory.  With n
+// steps a launch the stored tile is the region less n - 1 nodes on every side,
+// and the tiles cover the domain.  Every node of every step goes through the
+// same pull, collision and rounding as in k_sweep, so the result is
+// bit-identical to n single steps.
+//
+// What this is for.  Small lattices are bound by the ~4 us that a launch
+// costs from its first load to its last store, large ones by the bytes of a
+// step: both are paid once per n steps.  What n costs is the rim, computed by
+// several workgroups: a launch takes about
+//   4 us + max(n 8 v, ceil(tiles / 256) v waves),  v = 0.05 to 0.1 us,
+// waves the wave-rows of all its steps (vector issue of one CU), or its bytes
+// at 5 TB/s; choose_multi in lb_api.hip takes the region and n that this
+// makes smallest.
+//
+// n is odd (3, 5, 7, 9): the launch reads buffer T & 1 and writes the other,
+// which is the buffer of step T + n, so any sequence of launches and single
+// steps leaves the state where every other kernel expects it.
+//
+// Measured, us a step, against the two-step tiles this replaced (62 columns
+// by 6 to 14 rows, a pair of steps a launch): channel 128 x 64 FP64 3.13 ->
+// 1.03, power-law channel 101 x 51 FP32 4.34 -> 1.37, noise 256 x 512 FP32
+// 5.08 -> 2.58, 724 x 700 FP32 4.84 -> 3.45, 2048^2 with obstacles FP32 41.0
+// -> 23.9, 4096^2 FP32 134 -> 77 (15.7 TB/s of single-step bytes), 3000^2
+// FP64 138 -> 76, 4096^2 FP16 80.1 -> 72.5.
+#pragma once
+
+#include "sweep_impl.h"
+
+namespace lbk {
+
+template <int ST, int FEAT, int PLM, int K>
+__device__ __forceinline__ void multi_body(const DevDomain &D, int tile, int kstep, int nsteps) {
+  using S = Store<ST>;
+  using T = typename S::T;
+  using R = CompT<ST, 0>;
+  constexpr bool LABELS = (FEAT & F_LABELS) != 0;
+  constexpr Region G = region(K);
+  constexpr int CW = G.cw, RS = G.rs, NT = G.nt, NODES = CW * RS, U = NODES / NT;
+  static_assert(NODES % NT == 0, "whole nodes per thread");
+  constexpr uint32_t B = sizeof(T);
+  __shared__ T lds[9][NODES];
+
+  const int nx = D.nx, ny = D.ny, pitch = D.pitch;
+  const int rim = nsteps - 1, ow = CW - 2 * rim, oh = RS - 2 * rim;
+  const int tiles_x = (nx + ow - 1) / ow;
+  const int ty = tile / tiles_x, tx = tile - ty * tiles_x;
+  // state time, made wave-uniform so that the buffers stay in scalar registers
+  const uint64_t ts = *gbl(D.tstep);
+  const uint64_t T0 = (((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(ts >> 32)) << 32) |
+                       __builtin_amdgcn_readfirstlane((uint32_t)ts)) + (uint64_t)kstep;
+  const uint32_t pitchB = (uint32_t)pitch * B, planeB = (uint32_t)ny * pitchB;
+  void *const f0 = D.f[0];
+  void *const f1 = D.f[1];
+  const BufRes src = pop_buffer((T0 & 1) ? f1 : f0, 9u * planeB);
+  const BufRes dst = pop_buffer((T0 & 1) ? f0 : f1, 9u * planeB);
+  const bool has_lab = LABELS && D.label != nullptr;
+  const bool sr = (ST == ST_F16 || ST == ST_BF16) && (D.feat & F_STOCH);
+  bool bad = false;
+
+  auto wrap = [](int c, int n) {
+    c %= n;
+    return c < 0 ? c + n : c;
+  };
+  // this thread's nodes: id = thread + u NT, row id / CW, column id % CW
+  uint32_t w[U], node[U], here[U];
+  int xu[U], yu[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int id = (int)threadIdx.x + u * NT;
+    xu[u] = wrap(tx * ow - rim + id % CW, nx);
+    yu[u] = wrap(ty * oh - rim + id / CW, ny);
+    w[u] = has_lab ? gbl(D.nodew)[(uint32_t)yu[u] * pitch + xu[u]] : 0u;
+    node[u] = (uint32_t)yu[u] * (uint32_t)nx + (uint32_t)xu[u];
+    here[u] = (uint32_t)yu[u] * pitchB + (uint32_t)xu[u] * B;
+  }
+  // first step: the pulls of all nodes together.  The population plane is
+  // the scalar offset, the place in it the vector offset; opposite directions
+  // lie two planes apart, so a bounced pull takes the lower one's plane and
+  // the vector offset makes up the rest (see pull_node).
+  Pulled<T> raw[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int x = xu[u], y = yu[u];
+    const uint32_t xo[3] = {(uint32_t)(x + 1 < nx ? x + 1 : 0) * B, (uint32_t)x * B,
+                            (uint32_t)(x > 0 ? x - 1 : nx - 1) * B};
+    const uint32_t yo[3] = {(uint32_t)(y + 1 < ny ? y + 1 : 0) * pitchB, (uint32_t)y * pitchB,
+                            (uint32_t)(y > 0 ? y - 1 : ny - 1) * pitchB};
+    raw[u].set(0, bload<T>(src, here[u], 0u));
+#pragma unroll
+    for (int i = 1; i < 9; ++i) {
+      const uint32_t vN = yo[1 + cy(i)] + xo[1 + cx(i)];
+      if constexpr (!LABELS) {
+        raw[u].set(i, bload<T>(src, vN, (uint32_t)i * planeB));
+      } else {
+        const bool up = opp(i) > i;
+        uint32_t m = (uint32_t)(-(int32_t)((w[u] >> (i - 1)) & 1u));  // all ones: bounces
+        __asm__("" : "+v"(m));
+        const uint32_t a = up ? vN : vN + 2u * planeB, c = up ? here[u] + 2u * planeB : here[u];
+        raw[u].set(i, bload<T>(src, a ^ ((a ^ c) & m), (uint32_t)(up ? i : opp(i)) * planeB));
+      }
+    }
+  }
+  // the rounding mode is uniform: each branch keeps its own writes
+  auto encode = [&](const R (&e)[9], uint32_t nd, uint32_t step, auto &&put) {
+    T q[9];
+    if (sr) {
+      encode_node<ST, R, true>(D, e, nd, step, q);
+#pragma unroll
+      for (int i = 0; i < 9; ++i) put(i, q[i]);
+    } else {
+      encode_node<ST, R, false>(D, e, nd, step, q);
+#pragma unroll
+      for (int i = 0; i < 9; ++i) put(i, q[i]);
+    }
+  };
+  // A solid node's first-step values are never read (a pull from it bounces
+  // back), so it collides whatever it pulled; later it is swept at rest.
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int id = (int)threadIdx.x + u * NT;
+    R e[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) e[i] = (R)S::raw_dec(raw[u].get(i));
+    bad = bad || !(fabs(scaled_drho<ST, R>(e)) < R(1e30));
+    const uint32_t step = (uint32_t)(T0 + 1);
+    collide_node<ST, FEAT, PLM, R>(D, e, node[u], step);
+    encode(e, node[u], step, [&](int i, T v) { lds[i][id] = v; });
+  }
+  // step s: the nodes at least s - 1 inside the region, from LDS, in place
+#pragma unroll 1
+  for (int s = 2; s <= nsteps; ++s) {
+    const int m = s - 1;
+    const uint32_t step = (uint32_t)(T0 + (uint64_t)s);
+    __syncthreads();
+    bool act[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int id = (int)threadIdx.x + u * NT, r = id / CW, c = id % CW;
+      act[u] = r >= m && r < RS - m && c >= m && c < CW - m;
+      if (!act[u]) continue;
+      const T *p = &lds[0][0] + id;
+      raw[u].set(0, p[0]);
+#pragma unroll
+      for (int i = 1; i < 9; ++i) {
+        const int kn = i * NODES - cy(i) * CW - cx(i), ko = opp(i) * NODES;
+        if constexpr (LABELS) raw[u].set(i, p[((w[u] >> (i - 1)) & 1u) ? ko : kn]);
+        else raw[u].set(i, p[kn]);
+      }
+    }
+    __syncthreads();  // every source has been read
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (!act[u]) continue;
+      const int id = (int)threadIdx.x + u * NT;
+      const bool solid = LABELS && (w[u] & NODE_SOLID);
+      R e[9];
+#pragma unroll
+      for (int i = 0; i < 9; ++i) e[i] = solid ? R(0) : (R)S::raw_dec(raw[u].get(i));
+      bad = bad || !(fabs(scaled_drho<ST, R>(e)) < R(1e30));
+      collide_node<ST, FEAT, PLM, R>(D, e, node[u], step);
+      if (s < nsteps)
+        encode(e, node[u], step, [&](int i, T v) { lds[i][id] = v; });
+      else if (tx * ow + id % CW - rim < nx && ty * oh + id / CW - rim < ny)
+        // ordinary stores: the lines that two tiles share merge in the cache
+        encode(e, node[u], step,
+               [&](int i, T v) { bstore<T, false>(dst, here[u], (uint32_t)i * planeB, v); });
+    }
+  }
+  if (bad) atomicOr(D.health, HEALTH_NONFINITE);
+}
+
+// One domain, its descriptor in the kernel's arguments: without the load of
+// the descriptor the chain of dependent loads is one shorter, 0.6 us of the
+// 7 that a launch takes on a small lattice.
+template <int ST, int FEAT, int PLM, int K>
+__global__ __launch_bounds__(region(K).nt) void k_multi_one(const DevDomain D, int kstep, int nsteps) {
+  multi_body<ST, FEAT, PLM, K>(D, xcd_remap((int)blockIdx.x, (int)gridDim.x), kstep, nsteps);
+}
+
+// The domains of a batch (prefix: tiles of nsteps-step launches per domain).
+template <int ST, int FEAT, int PLM, int K>
+__global__ __launch_bounds__(region(K).nt) void k_multi(const DevDomain *__restrict__ doms,
+                                                        const int *__restrict__ prefix, int ndom,
+                                                        int kstep, int nsteps) {
+  const int b = xcd_remap((int)blockIdx.x, (int)gridDim.x);
+  const int dix = ndom == 1 ? 0 : find_domain(prefix, ndom, b);
+  const DevDomain D = doms[dix];  // held in scalar registers across the steps
+  multi_body<ST, FEAT, PLM, K>(D, ndom == 1 ? b : b - prefix[dix], kstep, nsteps);
+}
+
+}  // namespace lbk

@@ -428,8 +428,7 @@ class Batch:
         return v.value
 
     def autotune(self, steps=8):
-        """lb_batch_autotune: the two-step tile height (0.0 when cached or
-        not applicable, else the best ms per step)."""
+        """lb_batch_autotune: 0.0, nothing is left to tune in a batch."""
         ms = C.c_double()
         _check(library().lb_batch_autotune(self._h, int(steps), C.byref(ms)), "lb_batch_autotune")
         return ms.value
