@@ -9,6 +9,7 @@
 #include <string>
 #include <vector>
 
+#include "host_read.h"
 #include "lb.h"
 #include "launch3.h"
 
@@ -145,6 +146,7 @@ struct lb3_domain {
   bool wide = false;               // the sweep takes 64-bit byte offsets
   int q = 19;                      // lattice velocities
   std::vector<uint8_t> host_mask;  // [nz][ny][pitch]: walls and obstacles
+  lbk::HostRing ring;              // pinned buffers of the host reads
   Dom3 *ddesc() const { return (Dom3 *)(ws + L.desc); }
   Header3 *dhdr() const { return (Header3 *)(ws + L.hdr); }
   long long nodes() const { return (long long)desc.nx * desc.ny * desc.nz; }
@@ -424,15 +426,10 @@ static lb_status lb3_moments_impl(lb3_domain *d, double *rho, double *ux, double
   const long long n = d->nodes();
   double *st = (double *)(d->ws + d->L.stage);
   double *h[4] = {rho, ux, uy, uz};
-  for (long long n0 = 0; n0 < n; n0 += BAND) {
-    const long long cnt = std::min(BAND, n - n0);
+  HIPCHK3(lbk::read_fields(d->ring, h, 4, n, st, BAND, d->stream, [&](long long n0, long long cnt) {
     LB3_DISPATCH(d, k_moments3, dim3(blocks_of(cnt)), dim3(256), 0, d->stream,
                  d->ddesc(), st, n0, cnt);
-    HIPCHK3(hipGetLastError());
-    for (int k = 0; k < 4; ++k)
-      HIPCHK3(hipMemcpyAsync(h[k] + n0, st + k * cnt, cnt * 8, hipMemcpyDeviceToHost, d->stream));
-    HIPCHK3(hipStreamSynchronize(d->stream));
-  }
+  }));
   return check_health3(d);
 }
 
@@ -444,16 +441,12 @@ static lb_status lb3_get_populations_impl(lb3_domain *d, double *f) {
   if (!d || !f) return fail3(LB_EINVAL, "null argument");
   const long long n = d->nodes();
   double *st = (double *)(d->ws + d->L.stage);
-  for (long long n0 = 0; n0 < n; n0 += BAND) {
-    const long long cnt = std::min(BAND, n - n0);
+  double *h[27];
+  for (int i = 0; i < d->q; ++i) h[i] = f + (size_t)i * n;
+  HIPCHK3(lbk::read_fields(d->ring, h, d->q, n, st, BAND, d->stream, [&](long long n0, long long cnt) {
     LB3_DISPATCH(d, k_export3, dim3(blocks_of(cnt)), dim3(256), 0, d->stream,
                  d->ddesc(), st, n0, cnt);
-    HIPCHK3(hipGetLastError());
-    for (int i = 0; i < d->q; ++i)
-      HIPCHK3(hipMemcpyAsync(f + (size_t)i * n + n0, st + (size_t)i * cnt, cnt * 8,
-                             hipMemcpyDeviceToHost, d->stream));
-    HIPCHK3(hipStreamSynchronize(d->stream));
-  }
+  }));
   return check_health3(d);
 }
 
