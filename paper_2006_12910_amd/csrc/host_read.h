@@ -2,13 +2,13 @@
 //
 // A copy into pageable memory is staged by the runtime on one thread, waits
 // for each chunk, and faults in the pages of a fresh array as it goes: 168 MB
-// of moments (188 x 188 x 148) took 15.5 ms.  Here the chunks go through a
+// of moments (256 x 160 x 128) took 15.5 ms.  Here the chunks go through a
 // ring of pinned buffers at the link's rate (57 GB/s, 3 ms), and a few helper
 // threads copy them on, each into planes of its own.  While the GPU still
 // works on the steps before the read, they touch the pages of the result,
 // which is most of what a copy into a fresh array costs (one thread: 5 GB/s
-// fresh, 60 GB/s touched).  200 steps and a read into fresh arrays: 188 x 188 x
-// 148 FP32 39.2 -> 26.0 ms, 168^3 FP16 35.8 -> 23.2 ms.
+// fresh, 60 GB/s touched).  200 steps and a read into fresh arrays: 256 x 160 x
+// 128 FP32 39.2 -> 26.0 ms, 192 x 192 x 130 FP16 35.8 -> 23.2 ms.
 #pragma once
 
 #include <hip/hip_runtime.h>
