@@ -46,13 +46,13 @@ void init_l(const DevDomain *dom, const double *rho, const double *ux, const dou
                      dom, rho, ux, uy, row0, nrows);
 }
 void pre_l(const DevDomain *doms, const PItem *items, int nitems, int kstep, hipStream_t s) {
-  hipLaunchKernelGGL((k_pre<ST>), dim3(nitems), dim3(256), 0, s, doms, items, kstep);
+  hipLaunchKernelGGL((k_pre<ST>), dim3(nitems), dim3(PT), 0, s, doms, items, kstep);
 }
 void post_l(const DevDomain *doms, const PItem *items, int nitems, int kstep, hipStream_t s) {
-  hipLaunchKernelGGL((k_post<ST>), dim3(nitems), dim3(256), 0, s, doms, items, kstep);
+  hipLaunchKernelGGL((k_post<ST>), dim3(nitems), dim3(PT), 0, s, doms, items, kstep);
 }
 void post_pre_l(const DevDomain *doms, const PItem *items, int nitems, int kstep, hipStream_t s) {
-  hipLaunchKernelGGL((k_post_pre<ST>), dim3(nitems), dim3(256), 0, s, doms, items, kstep);
+  hipLaunchKernelGGL((k_post_pre<ST>), dim3(nitems), dim3(PT), 0, s, doms, items, kstep);
 }
 void mass_l(const DevDomain *doms, const int *prefix, int ndom, int blocks, double *alt,
             hipStream_t s) {

@@ -507,8 +507,11 @@ __device__ __forceinline__ int find_domain(const int *__restrict__ prefix, int n
   return lo;
 }
 
+// The image of d nearest to zero.  Most differences are their own image: those
+// skip the division (whose floor would be 0) with the same bits.
 __device__ __forceinline__ double min_image(double d, double len, bool periodic) {
-  return periodic ? d - len * floor(d / len + 0.5) : d;
+  if (!periodic || fabs(d) < 0.49 * len) return d;
+  return d - len * floor(d / len + 0.5);
 }
 
 }  // namespace lbk

@@ -3,18 +3,23 @@
 // Per step, for the state at time T (post-collision populations f*(T), labels
 // G(T), particle state P(T)), two kernels with one workgroup per particle
 // bracket the sweep:
-//   k_pre    before the sweep: enumerate the exterior pulls crossing the
-//            particle's surface inside its bounding box, compact them into an
-//            LDS list (deterministic block scan); for each link add the
-//            momentum exchange of Eq. MP1 and its torque (Eq. MP4) in FP64
-//            and write the moving-wall bounce-back (Eqs. MP7-MP8) into the
-//            link's two pull slots, so the sweep pulls unconditionally; sum
-//            the repulsion from solid nodes and from the other particles
-//            (Eq. MP2, one lane per particle pair); then one lane takes the
-//            Newton-Euler step of Eqs. MP5-MP6 into P(T+1).
+//   k_pre    before the sweep: list the nodes of the particle's bounding box
+//            with exterior pulls that cross its surface; for each such link
+//            add the momentum exchange of Eq. MP1 and its torque (Eq. MP4) in
+//            FP64 and write the moving-wall bounce-back (Eqs. MP7-MP8) into
+//            the link's two pull slots, so the sweep pulls unconditionally;
+//            the repulsion from solid nodes and from the
+//            other particles (Eq. MP2, one lane per particle pair) is summed
+//            beside it; then one lane takes the Newton-Euler step of Eqs.
+//            MP5-MP6 into P(T+1).
 //   k_post   after the sweep: the covered/uncovered-node force (Eq. MP3) of
 //            the nodes whose label changes from G(T) to G(T+1), and G(T+1)
 //            written into the label plane.
+// Both are chains of dependent loads and FP64 steps on one workgroup: what
+// counts is the length of the chain and the instructions a wave issues on it.
+// 16 discs of R = 8 in 2048 x 1024: k_pre 11.7 -> 8.7 us, k_post 7.0 -> 6.2,
+// from a list of single links that two block scans and one lane a link made,
+// sums by shuffles, and a division in every periodic image.
 // All reductions run in a fixed order, so results are bit-reproducible.
 #pragma once
 
@@ -22,36 +27,49 @@
 
 namespace lbk {
 
-constexpr int LINK_CAP = 6144;
+constexpr int PT = 512;  // threads per particle
 // The host admits no particle whose box side W = 2 reach + 2 has W^2 above
-// LINK_CAP (W <= 78), so the box with a one-node rim fits 80 x 80 labels.
+// 6144 (W <= 78), so the box with a one-node rim fits 80 x 80 labels.
 constexpr int LAB_BOX = 80 * 80;
 constexpr uint8_t LBL_OUT = 0xff;  // rim or box node outside a non-periodic domain
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+// v plus the value that a DPP move brings to the lane (zero where it brings none).
+template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, true);
+  return v + __hiloint2double(hi, lo);
 }
 
-// Sum of NV values over the 256 threads of a block, fixed order; result valid
-// in every thread.
+// Sum of NV values over the PT threads of a block, fixed order; result valid
+// in every thread.  Within a wave by DPP moves (shifts within the rows of 16,
+// then the rows' last lanes broadcast on), which cost a quarter of shuffles
+// through LDS; lane 63 holds the wave's sum.
 template <int NV>
 __device__ __forceinline__ void block_sum(double (&v)[NV], double (*scratch)[NV]) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
-  for (int k = 0; k < NV; ++k) v[k] = wave_sum(v[k]);
-  if (lane == 0) {
+  for (int k = 0; k < NV; ++k) {
+    v[k] = dpp_add<0x111, 0xf>(v[k]);  // row_shr 1, 2, 4, 8
+    v[k] = dpp_add<0x112, 0xf>(v[k]);
+    v[k] = dpp_add<0x114, 0xf>(v[k]);
+    v[k] = dpp_add<0x118, 0xf>(v[k]);
+    v[k] = dpp_add<0x142, 0xa>(v[k]);  // row_bcast 15, 31
+    v[k] = dpp_add<0x143, 0xc>(v[k]);
+  }
+  if (lane == 63) {
 #pragma unroll
     for (int k = 0; k < NV; ++k) scratch[w][k] = v[k];
   }
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < NV; ++k) v[k] = (scratch[0][k] + scratch[1][k]) + (scratch[2][k] + scratch[3][k]);
+  for (int k = 0; k < NV; ++k)
+    v[k] = ((scratch[0][k] + scratch[1][k]) + (scratch[2][k] + scratch[3][k])) +
+           ((scratch[4][k] + scratch[5][k]) + (scratch[6][k] + scratch[7][k]));
   __syncthreads();
 }
 
-// Exclusive prefix sum of one int per thread over the block (fixed order).
+// Exclusive prefix sum of one int per thread over the first 256 threads of the
+// block (fixed order).
 __device__ __forceinline__ int block_exscan(int v, int *sh, int &total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   int incl = v;
@@ -60,10 +78,10 @@ __device__ __forceinline__ int block_exscan(int v, int *sh, int &total) {
     const int t = __shfl_up(incl, o, 64);
     if (lane >= o) incl += t;
   }
-  if (lane == 63) sh[w] = incl;
+  if (lane == 63 && w < 4) sh[w] = incl;
   __syncthreads();
   int base = 0;
-  for (int k = 0; k < w; ++k) base += sh[k];
+  for (int k = 0; k < min(w, 4); ++k) base += sh[k];
   total = sh[0] + sh[1] + sh[2] + sh[3];
   __syncthreads();
   return base + incl - v;
@@ -81,9 +99,13 @@ __device__ __forceinline__ bool wrap_coord(int &v, int n, bool periodic) {
   return true;
 }
 
+// Not inlined: pow's registers and constants would be taken for the whole of
+// the kernels that rarely come here.
+__device__ __attribute__((noinline)) double lj_power(double r) { return pow(r, -13.0); }
+
 __device__ __forceinline__ double lj_mag(const DevDomain &D, double gap) {
   const double g = gap < D.lj_floor ? D.lj_floor : gap;
-  return D.lj_psi * pow(g / D.lj_rit, -13.0);
+  return D.lj_psi * lj_power(g / D.lj_rit);
 }
 
 struct PDisc {
@@ -126,14 +148,20 @@ __device__ __forceinline__ void pair_repulsion(const DevDomain &D, const PState 
   ly += m * dy / dist;
 }
 
-// Newton-Euler step (Eqs. MP5-MP6) of particle p from its state P = P(T),
-// its link, cover and solid-repulsion forces F and its particle-particle
-// repulsion (lx, ly), into P(T+1); with F_FAVG the update takes the mean of
-// this step's total force and torque and the previous step's, which P(T)
-// holds.
-__device__ __forceinline__ void advance_particle(const DevDomain &D, int p, const PState &P,
-                                                 PState *nxt, const PForce &F, double lx,
-                                                 double ly) {
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// Newton-Euler step (Eqs. MP5-MP6) of a particle: P(T+1) from its state
+// P = P(T), its link, cover and solid-repulsion forces F and its
+// particle-particle repulsion (lx, ly); with F_FAVG the update takes the mean
+// of this step's total force and torque and the previous step's, which P(T)
+// holds.  fast: the new velocity is outside what the coupling covers.  Called
+// by whole waves, whose lanes hold the same values: the three divisions, of
+// many instructions each, run in three lanes at once.
+__device__ __forceinline__ PState newton_euler(const DevDomain &D, const PState &P, const PForce &F,
+                                               double lx, double ly, bool &fast) {
   const bool perx = D.bc_x == BC_PERIODIC, pery = D.bc_y == BC_PERIODIC;
   const double fx = F.fx + F.cx_ + (lx + F.ljx);
   const double fy = F.fy + F.cy_ + (ly + F.ljy);
@@ -147,18 +175,153 @@ __device__ __forceinline__ void advance_particle(const DevDomain &D, int p, cons
   N.fx = fx;
   N.fy = fy;
   N.torque = tq;
+  fast = false;
   if (!(P.flags & 1)) {
     const double buoy = 1.0 - D.rho0 / (P.rho_ratio * D.rho0);
-    N.ux = P.ux + fxu / P.mass + buoy * D.gx;
-    N.uy = P.uy + fyu / P.mass + buoy * D.gy;
-    N.omega = P.omega + tqu / P.inertia;
+    const int lane = threadIdx.x & 63;
+    const double q = (lane == 0 ? fxu : lane == 1 ? fyu : tqu) / (lane < 2 ? P.mass : P.inertia);
+    N.ux = P.ux + lane_value(q, 0) + buoy * D.gx;
+    N.uy = P.uy + lane_value(q, 1) + buoy * D.gy;
+    N.omega = P.omega + lane_value(q, 2);
     N.x = P.x + P.ux;
     N.y = P.y + P.uy;
     if (perx) { if (N.x >= D.nx) N.x -= D.nx; if (N.x < 0.0) N.x += D.nx; }
     if (pery) { if (N.y >= D.ny) N.y -= D.ny; if (N.y < 0.0) N.y += D.ny; }
-    if (!(fabs(N.ux) < 0.5 && fabs(N.uy) < 0.5)) atomicOr(D.health, HEALTH_FAST_PARTICLE);
+    fast = !(fabs(N.ux) < 0.5 && fabs(N.uy) < 0.5);
   }
-  nxt[p] = N;
+  return N;
+}
+
+// Repulsion on a particle from the solid node (x, y) within lim of its centre.
+__device__ __forceinline__ void solid_repulsion(const DevDomain &D, const PState &P, double lim, int x,
+                                                int y, double &ljx, double &ljy) {
+  const bool perx = D.bc_x == BC_PERIODIC, pery = D.bc_y == BC_PERIODIC;
+  const double dx = min_image(P.x - x, D.nx, perx), dy = min_image(P.y - y, D.ny, pery);
+  const double dist = sqrt(dx * dx + dy * dy);
+  if (dist <= lim && dist > 0.0) {
+    const double m = lj_mag(D, dist - P.radius);
+    ljx += m * dx / dist;
+    ljy += m * dy / dist;
+  }
+}
+
+// The multiple of the period that min_image takes off d.
+__device__ __forceinline__ double image_shift(double d, double len, bool periodic) {
+  if (!periodic || fabs(d) < 0.49 * len) return 0.0;
+  return len * floor(d / len + 0.5);
+}
+
+// j / w for box positions (j < 8192, w < 128), inv = 1.0f / w.
+__device__ __forceinline__ int box_row(int j, float inv) { return (int)((j + 0.5f) * inv); }
+
+// Exterior nodes with a link, box position and mask of the directions (bit
+// i - 1: the pull along i comes out of the particle): those of an annulus of
+// width sqrt(2) around the disc.
+template <int CAP> struct LinkList {
+  uint32_t rec[CAP];
+  int count[PT / 64];
+};
+
+// The links of the particle P in its box of W x W nodes.  First every thread
+// takes nodes of the box: mask(bi, bk) is a node's mask of links (and adds a
+// solid node's repulsion); the nodes that have some are listed in a fixed
+// order.  Then wave d takes the links along direction d + 1 of all of them,
+// a lane each: most of the box has none, and a wave that met its few nodes in
+// place would run the code of all eight directions for them (1.5 us more for
+// three steps of a disc of R = 5).  For each link the momentum exchange and torque go onto acc[0 .. 2]
+// and the bounce-back into its two slots: load(x, y, bi, bk, i, k) and put(...,
+// v) are the value of direction i at the node (k = 0) or at its source x - e_k.
+// A link's surface point is half a node from (x, y), a disc's radius from the
+// centre, so both have the same periodic image.
+template <int CAP, class Mask, class At, class Load, class Put>
+__device__ __forceinline__ void box_links(const DevDomain &D, const PState &P, int W, int bx0, int by0,
+                                          LinkList<CAP> &list, double (&acc)[7], Mask mask, At at,
+                                          Load load, Put put) {
+  const bool perx = D.bc_x == BC_PERIODIC, pery = D.bc_y == BC_PERIODIC;
+  const int tid = (int)threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nbox = W * W;
+  const float inv = 1.0f / (float)W;
+  uint64_t m0 = 0, m1 = 0;  // masks of the thread's nodes, at most 12 (6144 / PT)
+  int cnt = 0;
+  for (int j = tid, it = 0; it * PT < nbox; j += PT, ++it) {
+    uint32_t m = 0;
+    if (j < nbox) {
+      const int bk = box_row(j, inv);
+      m = mask(j - bk * W, bk);
+    }
+    cnt += __popcll(__ballot(m != 0));
+    if (it < 8) m0 |= (uint64_t)m << (8 * it);
+    else m1 |= (uint64_t)m << (8 * (it - 8));
+  }
+  if (lane == 0) list.count[wave] = cnt;
+  __syncthreads();
+  int pos = 0, total = 0;
+#pragma unroll
+  for (int k = 0; k < PT / 64; ++k) {
+    const int c = list.count[k];
+    pos += k < wave ? c : 0;
+    total += c;
+  }
+  for (int j = tid, it = 0; it * PT < nbox; j += PT, ++it) {
+    const uint32_t m = (uint32_t)((it < 8 ? m0 >> (8 * it) : m1 >> (8 * (it - 8))) & 255u);
+    const uint64_t b = __ballot(m != 0);
+    const int mine = pos + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+    if (m && mine < CAP) list.rec[mine] = ((uint32_t)j << 8) | m;
+    pos += __popcll(b);
+  }
+  __syncthreads();
+  if (total > CAP && tid == 0) atomicOr(D.health, HEALTH_LINK_OVERFLOW);
+  total = min(total, CAP);
+  const int dir = wave + 1, o = opp(dir);
+  const int dcx = cx(dir), dcy = cy(dir);
+  const double w = dir <= 4 ? wgt<double>(1) : wgt<double>(5);
+  for (int e = lane; e < total; e += 64) {
+    const uint32_t rec = list.rec[e];
+    if (!((rec >> wave) & 1u)) continue;
+    const int j = (int)(rec >> 8), bk = box_row(j, inv), bi = j - bk * W;
+    int x = bx0 + bi, y = by0 + bk;
+    wrap_coord(x, D.nx, perx);
+    wrap_coord(y, D.ny, pery);
+    const auto here = at(x, y, bi, bk, 0, 0), so = at(x, y, bi, bk, dcx, dcy);
+    const double a = load(here, o), b = load(so, dir);
+    const double fopp = w * D.rho0 + a;
+    const double sx = image_shift(x - P.x, D.nx, perx), sy = image_shift(y - P.y, D.ny, pery);
+    const double rx = (x - 0.5 * dcx - P.x) - sx, ry = (y - 0.5 * dcy - P.y) - sy;
+    const double vx = P.ux - P.omega * ry, vy = P.uy + P.omega * rx;
+    const double ue = vx * dcx + vy * dcy;
+    const double M = 6.0 * D.rho0 * w * ue;
+    const double mag = 2.0 * fopp + M;
+    const double dpx = -dcx * mag, dpy = -dcy * mag;
+    acc[0] += dpx;
+    acc[1] += dpy;
+    acc[2] += rx * dpy - ry * dpx;
+    put(so, dir, a + M);
+    put(here, o, b - M);
+  }
+}
+
+// Force and torque of a node (x, y) that the particle P covers (sign 1) or
+// uncovers (-1), load(i) its populations' deviations, onto acc.
+template <class Load>
+__device__ __forceinline__ void cover_term(const DevDomain &D, const PState &P, int x, int y,
+                                           double sign, double (&acc)[3], Load load) {
+  const bool perx = D.bc_x == BC_PERIODIC, pery = D.bc_y == BC_PERIODIC;
+  double drho = 0.0, jx = 0.0, jy = 0.0;
+  for (int i = 0; i < 9; ++i) {
+    const double v = load(i);
+    drho += v;
+    jx += v * cx(i);
+    jy += v * cy(i);
+  }
+  const double rho = D.rho0 + drho;
+  const double ux = jx / rho - 0.5 * D.gx, uy = jy / rho - 0.5 * D.gy;
+  const double fx = sign * rho * (ux - P.ux), fy = sign * rho * (uy - P.uy);
+  const double rx = min_image(x - P.x, D.nx, perx), ry = min_image(y - P.y, D.ny, pery);
+  acc[0] += fx;
+  acc[1] += fy;
+  acc[2] += rx * fy - ry * fx;
 }
 
 // Before the sweep of step T -> T+1, one workgroup per particle p.
@@ -177,9 +340,8 @@ __device__ __forceinline__ void pre_body(const DevDomain *__restrict__ doms,
   using S = Store<ST>;
   using T = typename S::T;
   using RS = typename S::R;
-  __shared__ uint32_t links[LINK_CAP];
-  __shared__ int scan_sh[4];
-  __shared__ double red[4][7];
+  __shared__ double red[PT / 64][7];
+  __shared__ LinkList<1024> links;
   // labels G(T) of the box and a one-node rim (out of the domain: LBL_OUT)
   __shared__ uint8_t lab[LAB_BOX];
   const PItem it = items[blockIdx.x];
@@ -209,64 +371,20 @@ __device__ __forceinline__ void pre_body(const DevDomain *__restrict__ doms,
   const int reach = max((int)ceil(P.radius) + 2, (int)ceil(P.radius + D.lj_rit) + 1);
   const int W = 2 * reach + 2;
   const int bx0 = (int)floor(P.x) - reach, by0 = (int)floor(P.y) - reach;
-  const int nbox = W * W;
-  const int chunk = (nbox + 255) / 256;
   const double lim = P.radius + D.lj_rit;
 
   // stage the labels: box position (i, k) -> lab[(k + 1) * WR + i + 1]
   const int WR = W + 2;
-  for (int j = threadIdx.x; j < WR * WR; j += 256) {
-    int x = bx0 - 1 + j % WR, y = by0 - 1 + j / WR;
+  const float invr = 1.0f / (float)WR;
+  for (int j = threadIdx.x; j < WR * WR; j += PT) {
+    const int k = box_row(j, invr);
+    int x = bx0 - 1 + j - k * WR, y = by0 - 1 + k;
     const bool in = wrap_coord(x, D.nx, perx) && wrap_coord(y, D.ny, pery);
     lab[j] = in ? D.label[(size_t)y * D.pitch + x] : LBL_OUT;
   }
   __syncthreads();
   auto lab_at = [&](int i, int k) { return lab[(k + 1) * WR + i + 1]; };
 
-  // pass 1: count crossing exterior pulls of this thread's contiguous nodes,
-  // and sum the repulsion from solid nodes
-  int cnt = 0;
-  double ljx = 0.0, ljy = 0.0;
-  for (int j = threadIdx.x * chunk; j < min(nbox, (threadIdx.x + 1) * chunk); ++j) {
-    const int bi = j % W, bk = j / W;
-    const uint8_t lx = lab_at(bi, bk);
-    if (lx == LBL_OUT) continue;
-    if (lx == LBL_SOLID) {
-      int x = bx0 + bi, y = by0 + bk;
-      wrap_coord(x, D.nx, perx);
-      wrap_coord(y, D.ny, pery);
-      const double dx = min_image(P.x - x, D.nx, perx), dy = min_image(P.y - y, D.ny, pery);
-      const double dist = sqrt(dx * dx + dy * dy);
-      if (dist <= lim && dist > 0.0) {
-        const double m = lj_mag(D, dist - P.radius);
-        ljx += m * dx / dist;
-        ljy += m * dy / dist;
-      }
-      continue;
-    }
-    if (lx != LBL_FLUID) continue;
-    for (int i = 1; i < 9; ++i)
-      if (lab_at(bi - cx(i), bk - cy(i)) == mine) ++cnt;
-  }
-  int total;
-  int pos = block_exscan(cnt, scan_sh, total);
-  // pass 2: write this thread's links in node order into the LDS list
-  for (int j = threadIdx.x * chunk; j < min(nbox, (threadIdx.x + 1) * chunk); ++j) {
-    if (!cnt) break;
-    const int bi = j % W, bk = j / W;
-    if (lab_at(bi, bk) != LBL_FLUID) continue;
-    for (int i = 1; i < 9; ++i) {
-      if (lab_at(bi - cx(i), bk - cy(i)) == mine) {
-        if (pos < LINK_CAP) links[pos] = ((uint32_t)j << 4) | (uint32_t)i;
-        ++pos;
-      }
-    }
-  }
-  __syncthreads();
-  // the host admits no radius whose box could hold more links than the list
-  if (total > LINK_CAP && threadIdx.x == 0) atomicOr(D.health, HEALTH_LINK_OVERFLOW);
-  const int nl = min(total, LINK_CAP);
-  // pass 3: momentum exchange (FP64) and moving-wall bounce-back of each link
   // repulsion from the other particles, one lane per pair
   double plx = 0.0, ply = 0.0;
   if (pair_lane) {
@@ -274,44 +392,46 @@ __device__ __forceinline__ void pre_body(const DevDomain *__restrict__ doms,
     const PDisc Q{odd ? qb.x : qa.x, odd ? qb.y : qa.y, odd ? qb.radius : qa.radius};
     pair_repulsion(D, P, Q, plx, ply);
   }
-  double acc[7] = {0.0, 0.0, 0.0, ljx, ljy, plx, ply};
-  for (int e = threadIdx.x; e < nl; e += 256) {
-    const uint32_t rec = links[e];
-    const int j = (int)(rec >> 4), dir = (int)(rec & 15u);
-    int x = bx0 + j % W, y = by0 + j / W;
-    wrap_coord(x, D.nx, perx);
-    wrap_coord(y, D.ny, pery);
-    int sx = x - cx(dir), sy = y - cy(dir);
-    wrap_coord(sx, D.nx, perx);
-    wrap_coord(sy, D.ny, pery);
-    const uint32_t here = (uint32_t)y * D.pitch + x, so = (uint32_t)sy * D.pitch + sx;
-    const int o = opp(dir);
-    const double a = (double)S::load(f + o * plane, here, o);
-    const double b = (double)S::load(f + dir * plane, so, dir);
-    const double fopp = wgt<double>(o) * D.rho0 + a;
-    const double bxr = x - 0.5 * cx(dir), byr = y - 0.5 * cy(dir);
-    const double rx = min_image(bxr - P.x, D.nx, perx), ry = min_image(byr - P.y, D.ny, pery);
-    const double vx = P.ux - P.omega * ry, vy = P.uy + P.omega * rx;
-    const double ue = vx * cx(dir) + vy * cy(dir);
-    const double mag = 2.0 * fopp + 6.0 * D.rho0 * wgt<double>(dir) * ue;
-    const double dpx = -cx(dir) * mag, dpy = -cy(dir) * mag;
-    acc[0] += dpx;
-    acc[1] += dpy;
-    acc[2] += rx * dpy - ry * dpx;
-    const double M = 6.0 * D.rho0 * wgt<double>(dir) * ue;
-    S::put(f + dir * plane, so, dir, (RS)(a + M), 0u);
-    S::put(f + o * plane, here, o, (RS)(b - M), 0u);
-  }
+  double acc[7] = {0.0, 0.0, 0.0, 0.0, 0.0, plx, ply};
+  box_links<1024>(
+      D, P, W, bx0, by0, links, acc,
+      [&](int bi, int bk) -> uint32_t {
+        const uint8_t lx = lab_at(bi, bk);
+        if (lx == LBL_SOLID) {
+          int x = bx0 + bi, y = by0 + bk;
+          wrap_coord(x, D.nx, perx);
+          wrap_coord(y, D.ny, pery);
+          solid_repulsion(D, P, lim, x, y, acc[3], acc[4]);
+        }
+        if (lx != LBL_FLUID) return 0u;
+        uint32_t m = 0;
+#pragma unroll
+        for (int i = 1; i < 9; ++i) m |= (uint32_t)(lab_at(bi - cx(i), bk - cy(i)) == mine) << (i - 1);
+        return m;
+      },
+      [&](int x, int y, int, int, int dx, int dy) {
+        int sx = x - dx, sy = y - dy;
+        wrap_coord(sx, D.nx, perx);
+        wrap_coord(sy, D.ny, pery);
+        return (size_t)((uint32_t)sy * D.pitch + sx);
+      },
+      [&](size_t at, int i) { return (double)S::load(f + i * plane, at, i); },
+      [&](size_t at, int i, double v) { S::put(f + i * plane, at, i, (RS)v, 0u); });
   block_sum<7>(acc, red);
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < 64) {
     PForce F = Fpre;
     F.fx = acc[0];
     F.fy = acc[1];
     F.torque = acc[2];
     F.ljx = acc[3];
     F.ljy = acc[4];
-    D.pforce[it.p] = F;
-    advance_particle(D, it.p, P, D.pstate[(T0 + 1) & 1], F, acc[5], acc[6]);
+    bool fast;
+    const PState N = newton_euler(D, P, F, acc[5], acc[6], fast);
+    if (threadIdx.x == 0) {
+      D.pforce[it.p] = F;
+      D.pstate[(T0 + 1) & 1][it.p] = N;
+      if (fast) atomicOr(D.health, HEALTH_FAST_PARTICLE);
+    }
   }
 }
 
@@ -356,7 +476,7 @@ __device__ __forceinline__ void post_body(const DevDomain *__restrict__ doms,
                                           const PItem *__restrict__ items, int kstep) {
   using S = Store<ST>;
   using T = typename S::T;
-  __shared__ double red[4][3];
+  __shared__ double red[PT / 64][3];
   __shared__ int scan_sh[4];
   // discs of P(T) and P(T+1) that can reach a node of this box, in index
   // order (so the first-particle rule is unchanged)
@@ -408,8 +528,10 @@ __device__ __forceinline__ void post_body(const DevDomain *__restrict__ doms,
     __syncthreads();
   }
   double acc[3] = {0.0, 0.0, 0.0};
-  for (int j = threadIdx.x; j < W * W; j += 256) {
-    int x = bx0 + j % W, y = by0 + j / W;
+  const float inv = 1.0f / (float)W;
+  for (int j = threadIdx.x; j < W * W; j += PT) {
+    const int k = box_row(j, inv);
+    int x = bx0 + j - k * W, y = by0 + k;
     if (!wrap_coord(x, D.nx, perx) || !wrap_coord(y, D.ny, pery)) continue;
     const uint32_t here = (uint32_t)y * D.pitch + x;
     if (D.nodew[here] & NODE_SOLID) continue;
@@ -418,20 +540,8 @@ __device__ __forceinline__ void post_body(const DevDomain *__restrict__ doms,
     if (l1 != l0) D.label[here] = l1;
     if ((l0 == mine) == (l1 == mine)) continue;
     const double sign = l1 == mine ? 1.0 : -1.0;
-    double drho = 0.0, jx = 0.0, jy = 0.0;
-    for (int i = 0; i < 9; ++i) {
-      const double v = (double)S::load(src + i * plane, here, i);
-      drho += v;
-      jx += v * cx(i);
-      jy += v * cy(i);
-    }
-    const double rho = D.rho0 + drho;
-    const double ux = jx / rho - 0.5 * D.gx, uy = jy / rho - 0.5 * D.gy;
-    const double fx = sign * rho * (ux - P.ux), fy = sign * rho * (uy - P.uy);
-    const double rx = min_image(x - P.x, D.nx, perx), ry = min_image(y - P.y, D.ny, pery);
-    acc[0] += fx;
-    acc[1] += fy;
-    acc[2] += rx * fy - ry * fx;
+    cover_term(D, P, x, y, sign, acc,
+               [&](int i) { return (double)S::load(src + i * plane, here, i); });
   }
   block_sum<3>(acc, red);
   if (threadIdx.x == 0) {
@@ -443,13 +553,13 @@ __device__ __forceinline__ void post_body(const DevDomain *__restrict__ doms,
 }
 
 template <int ST>
-__global__ __launch_bounds__(256) void k_pre(const DevDomain *__restrict__ doms,
+__global__ __launch_bounds__(PT) void k_pre(const DevDomain *__restrict__ doms,
                                              const PItem *__restrict__ items, int kstep) {
   pre_body<ST>(doms, items, kstep);
 }
 
 template <int ST>
-__global__ __launch_bounds__(256) void k_post(const DevDomain *__restrict__ doms,
+__global__ __launch_bounds__(PT) void k_post(const DevDomain *__restrict__ doms,
                                               const PItem *__restrict__ items, int kstep) {
   post_body<ST>(doms, items, kstep);
 }
@@ -465,7 +575,7 @@ __global__ __launch_bounds__(256) void k_post(const DevDomain *__restrict__ doms
 // would race (a disc's bounce-back writes can reach nodes a neighbour's
 // cover force still reads), so those launches keep the two kernels.
 template <int ST>
-__global__ __launch_bounds__(256) void k_post_pre(const DevDomain *__restrict__ doms,
+__global__ __launch_bounds__(PT) void k_post_pre(const DevDomain *__restrict__ doms,
                                                   const PItem *__restrict__ items, int kstep) {
   post_body<ST>(doms, items, kstep);
   __syncthreads();
