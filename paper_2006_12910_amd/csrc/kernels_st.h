@@ -4,6 +4,7 @@
 #pragma once
 
 #include "aux_impl.h"
+#include "discn_impl.h"
 #include "launch.h"
 #include "particles_impl.h"
 #include "sweep_impl.h"
@@ -37,6 +38,14 @@ void multi_l(const DevDomain *doms, const int *prefix, int ndom, const DevDomain
       hipLaunchKernelGGL((k_multi<ST, FEAT, PLM, 2>), dim3(blocks), dim3(region(2).nt), 0, s, doms,
                          prefix, ndom, kstep, nsteps);
   }
+}
+template <int FEAT, int PLM>
+void multi_disc_l(const DevDomain *doms, const int *prefix, int ndom, const PItem *items, int nitems,
+                  const DevDomain *one, int kstep, int blocks, hipStream_t s) {
+  constexpr int K = disc_region(ST);
+  static const DevDomain none{};
+  hipLaunchKernelGGL((k_multi_disc<ST, FEAT, PLM, K>), dim3(nitems + blocks), dim3(region(K).nt), 0, s,
+                     doms, prefix, ndom, items, nitems, one != nullptr ? *one : none, kstep);
 }
 template <int FEAT, int PLM, int WIDE>
 void init_l(const DevDomain *dom, const double *rho, const double *ux, const double *uy, int row0,
@@ -90,6 +99,9 @@ template <int FEAT, int PLM, int WIDE> void fill(KernelSet *k) {
     k->multi = multi_l<FEAT, PLM>;
   else
     k->multi = nullptr;
+  k->multi_disc = nullptr;
+  if constexpr (WIDE == 0 && (FEAT & F_LABELS) != 0 && !((FEAT & F_POWER) != 0 && (FEAT & F_NOISE) != 0))
+    k->multi_disc = multi_disc_l<FEAT, PLM>;
   k->init = init_l<FEAT, PLM, WIDE>;
   k->pre = pre_l;
   k->post = post_l;

@@ -16,6 +16,11 @@ struct KernelSet {
   // the feature set has no such kernel
   void (*multi)(const DevDomain *doms, const int *prefix, int ndom, const DevDomain *one, int k,
                 int kstep, int nsteps, int blocks, hipStream_t s);
+  // DISC_STEPS steps per launch of domains with at most one particle each, the
+  // `nitems` particles of `items`, over `blocks` tiles of region
+  // disc_region(storage); `one` the descriptor of a single domain or null; null where the feature set has no such kernel
+  void (*multi_disc)(const DevDomain *doms, const int *prefix, int ndom, const PItem *items,
+                     int nitems, const DevDomain *one, int kstep, int blocks, hipStream_t s);
   void (*init)(const DevDomain *dom, const double *rho, const double *ux, const double *uy,
                int row0, int nrows, int pitch, hipStream_t s);
   // particle coupling before and after the sweep (one workgroup per particle)

@@ -288,6 +288,7 @@ struct lb_domain {
   int in_batches = 0;
   int rows2 = 0;          // LB_OPT_TWO_STEP_ROWS
   MultiPlan multi;        // how several steps a launch are taken
+  bool disc_fits = false; // one particle, which several steps a launch can take
   std::vector<uint8_t> host_labels;  // walls + obstacles, [ny][pitch]
   // asynchronous moment output: moments computed (on stream), copied out
   // (on the caller's copy stream); a copy in flight until lb_moments_wait
@@ -309,6 +310,7 @@ struct lb_batch {
   KernelSet ks{};
   int total_tiles = 0, total_mass_blocks = 0, nitems = 0;
   bool multi_step = false;  // every domain takes several steps a launch
+  bool disc = false;        // and some of them hold a particle
   MultiPlan multi;
   int multi_tiles[MULTI_MAX + 1] = {};  // tiles of the launches of n steps
   int rows2 = 0;                        // LB_OPT_TWO_STEP_ROWS
@@ -388,6 +390,7 @@ struct MultiSteps {
   MultiPlan plan;
   const DevDomain *one = nullptr;         // the descriptor of a single domain
   const lb_batch *batch = nullptr;        // or the batch
+  bool disc = false;                      // with particles
   int tiles(int n) const { return batch ? batch->multi_tiles[n] : multi_tiles(plan.k, n, one->nx, one->ny); }
   const int *prefix(int n) const { return batch ? batch->dprefixn(n) : nullptr; }
 };
@@ -399,6 +402,20 @@ struct MultiSteps {
 // takes to enqueue it, and captured chunks of fixed lengths would break the
 // calls into shorter launches (250 steps: 48 launches and 10 counter updates
 // instead of 36 and 1).
+//
+// With particles a launch takes DISC_STEPS, and a part of 1 is k_pre, the
+// sweep and k_post.
+void disc_steps(const StepPlan &p, const DevDomain *one, const int *prefix, int tiles, int k, int len,
+                hipStream_t s) {
+  if (len > 1) {
+    p.ks->multi_disc(p.doms, prefix, p.ndom, p.items, p.nitems, one, k, tiles, s);
+    return;
+  }
+  p.ks->pre(p.doms, p.items, p.nitems, k, s);
+  p.ks->sweep(p.doms, p.prefix, p.ndom, k, p.blocks, 0, s);
+  p.ks->post(p.doms, p.items, p.nitems, k, s);
+}
+
 lb_status run_multi(const StepPlan &p, const MultiSteps &m, int64_t n, hipStream_t s) {
   for (int64_t done = 0; done < n;) {
     const int c = (int)std::min<int64_t>(n - done, 1 << 16);
@@ -409,7 +426,9 @@ lb_status run_multi(const StepPlan &p, const MultiSteps &m, int64_t n, hipStream
     const int longer = (c - parts * lo) / 2;
     for (int i = 0, k = 0; i < parts; ++i) {
       const int len = lo + (i < longer ? 2 : 0);
-      if (len > 1)
+      if (m.disc)
+        disc_steps(p, m.one, m.prefix(len), m.tiles(len), k, len, s);
+      else if (len > 1)
         p.ks->multi(p.doms, m.prefix(len), p.ndom, m.one, m.plan.k, k, len, m.tiles(len), s);
       else
         p.ks->sweep(p.doms, p.prefix, p.ndom, k, p.blocks, 0, s);
@@ -541,6 +560,32 @@ bool multi_ok(const lb_domain *d) {
   const bool edges = (d->desc.bc_x == LB_PERIODIC && d->desc.bc_y == LB_PERIODIC) ||
                      (d->hd.label != nullptr && d->desc.bc_x != LB_PRESSURE);
   return d->two_step && d->ks.multi != nullptr && d->np == 0 && d->desc.max_particles == 0 && edges;
+}
+
+// The same with one particle whose coupling fits a region (discn_impl.h).
+bool disc_ok(const lb_domain *d) {
+  return d->two_step && d->ks.multi_disc != nullptr && d->np == 1 && d->disc_fits &&
+         d->desc.bc_x != LB_PRESSURE;
+}
+
+// The particle's radius and box against the region, and the region and the box
+// against the domain, which must not hold a node of either twice; a start
+// faster than what k_pre lets pass stays with the single steps.
+bool disc_fits(const lb_domain *d, const std::vector<PState> &all) {
+  if (all.size() != 1) return false;
+  const PState &q = all[0];
+  const int reach = std::max((int)std::ceil(q.radius) + 2, (int)std::ceil(q.radius + d->desc.lj_rit) + 1);
+  const int box = disc_box(reach), side = disc_side((int)std::ceil(q.radius));
+  const int least = std::max(side, box);
+  return side <= DISC_SIDE && box <= DISC_BOX && d->desc.nx >= least && d->desc.ny >= least &&
+         std::fabs(q.ux) < 0.5 && std::fabs(q.uy) < 0.5;
+}
+
+MultiPlan disc_plan(int storage) {
+  MultiPlan p;
+  p.k = disc_region(storage);
+  p.nmax = DISC_STEPS;
+  return p;
 }
 
 // FP64 density sum of the current state; its final kernel also latches a
@@ -867,8 +912,9 @@ lb_status check_cover(const lb_domain *d, const std::vector<PState> &all, int k,
 
 // Work items (one per particle), descriptor upload, labels of the current
 // particle state; drops the step graphs (the launch sequence changes).
-lb_status particles_changed(lb_domain *d) {
+lb_status particles_changed(lb_domain *d, const std::vector<PState> &all) {
   d->hd.np = d->np;
+  d->disc_fits = disc_fits(d, all);
   if (d->np > 0) {
     std::vector<PItem> items(d->np);
     for (int q = 0; q < d->np; ++q) items[q] = PItem{0, q};
@@ -916,7 +962,7 @@ static lb_status lb_add_particles_impl(lb_domain *d, const lb_particle *p, int32
   std::memset(zf.data(), 0, n * sizeof(PForce));
   HIPCHK(hipMemcpyAsync(d->hd.pforce + first, zf.data(), n * sizeof(PForce), hipMemcpyHostToDevice, d->stream));
   d->np += n;
-  if ((st = particles_changed(d)) != LB_OK) return st;
+  if ((st = particles_changed(d, cur)) != LB_OK) return st;
   if (first_id) *first_id = first;
   return LB_OK;
 }
@@ -987,7 +1033,7 @@ static lb_status lb_set_particle_state_impl(lb_domain *d, const lb_particle_stat
                           d->stream));
   }
   d->np = n;
-  return particles_changed(d);
+  return particles_changed(d, cur);
 }
 
 lb_status lb_set_particle_state(lb_domain *d, const lb_particle_state *in, int32_t n) {
@@ -1040,6 +1086,12 @@ static lb_status lb_step_impl(lb_domain *d, int64_t nsteps) {
       MultiSteps m;
       m.plan = d->multi;
       m.one = &d->hd;
+      s = run_multi(p, m, nsteps, d->stream);
+    } else if (disc_ok(d) && !d->overlap && nsteps >= DISC_STEPS) {
+      MultiSteps m;
+      m.plan = disc_plan(d->desc.storage);
+      m.one = &d->hd;
+      m.disc = true;
       s = run_multi(p, m, nsteps, d->stream);
     } else {
       s = run_steps(d->graphs, d->use_graph, d->chunk, d->stream, d->cap, p, nsteps);
@@ -1515,12 +1567,14 @@ static lb_status lb_batch_create_impl(lb_domain *const *domains, int32_t n, void
     prefix[i + 1] = prefix[i] + domains[i]->ntiles();
     prefix[n + 2 + i] = prefix[n + 1 + i] + domains[i]->hd.mass_blocks;
     for (int q = 0; q < domains[i]->np; ++q) items.push_back(PItem{i, q});
-    multi = multi && multi_ok(domains[i]);
+    multi = multi && (multi_ok(domains[i]) || disc_ok(domains[i]));
+    b->disc = b->disc || domains[i]->np > 0;
     sizes.emplace_back(domains[i]->desc.nx, domains[i]->desc.ny);
     feat |= domains[i]->feat;
   }
-  b->multi_step = multi;
-  b->multi = choose_multi(domains[0]->desc.storage, feat, sizes);
+  b->multi_step = multi && !(b->disc && b->ks.multi_disc == nullptr);
+  b->multi = b->disc ? disc_plan(domains[0]->desc.storage)
+                     : choose_multi(domains[0]->desc.storage, feat, sizes);
   for (int len = 3; len <= b->multi.nmax; len += 2) {
     int *pre = prefix.data() + (size_t)(len + 1) / 2 * (n + 1);
     for (int i = 0; i < n; ++i)
@@ -1572,10 +1626,11 @@ static lb_status lb_batch_step_impl(lb_batch *b, int64_t nsteps) {
     p.fuse_pp = true;
     for (auto *m : b->doms) p.fuse_pp = p.fuse_pp && m->np <= 1;
     lb_status s;
-    if (b->multi_step) {
+    if (b->multi_step && (!b->disc || nsteps >= DISC_STEPS)) {
       MultiSteps m;
       m.plan = b->multi;
       m.batch = b;
+      m.disc = b->disc;
       s = run_multi(p, m, nsteps, b->stream);
     } else {
       s = run_steps(b->graphs, b->use_graph, b->chunk, b->stream, b->cap, p, nsteps);

@@ -75,6 +75,15 @@ __host__ __device__ constexpr Region region(int k) {
 constexpr bool region_fits(int storage, int k) { return !(storage == ST_F64 && k == 2); }
 constexpr int MULTI_MAX = 9;  // most steps a launch takes
 
+// Steps per launch of domains with one particle (discn_impl.h), the tiles'
+// region, and the largest sides of the particle's label box and own region.
+constexpr int DISC_STEPS = 3;
+constexpr int disc_region(int storage) { return storage == ST_F64 ? 1 : 2; }
+constexpr int DISC_BOX = 52;
+constexpr int DISC_SIDE = 32;
+__host__ __device__ constexpr int disc_side(int radius_ceil) { return 2 * (radius_ceil + 8); }
+__host__ __device__ constexpr int disc_box(int reach) { return 2 * (reach + DISC_STEPS) + 4; }
+
 // Values of LB_OPT_TWO_STEP_ROWS, which no longer shapes anything.
 constexpr int two_step_rows_of(int storage, int k) {  // k = 0, 1, 2
   return storage == ST_F64 ? 4 + 2 * k : (storage == ST_F32 ? 6 + 4 * k : 10 + 4 * k);

@@ -1,5 +1,6 @@
 // sweepn_impl.h -- several time steps per launch, for the domains that need
-// nothing between two steps (no particles, no density faces): obstacles,
+// nothing between two steps (no density faces, and no particles but those of
+// discn_impl.h): obstacles,
 // walls as label rows, either collision, the power law, thermal noise.
 //
 // A workgroup owns a region of CW x RS nodes.  The first step of the region is
@@ -37,8 +38,32 @@
 
 namespace lbk {
 
-template <int ST, int FEAT, int PLM, int K>
-__device__ __forceinline__ void multi_body(const DevDomain &D, int tile, int kstep, int nsteps) {
+// State time, made wave-uniform so that the buffers stay in scalar registers.
+__device__ __forceinline__ uint64_t uniform_time(const DevDomain &D, int kstep) {
+  const uint64_t ts = *gbl(D.tstep);
+  return (((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(ts >> 32)) << 32) |
+          __builtin_amdgcn_readfirstlane((uint32_t)ts)) + (uint64_t)kstep;
+}
+
+// c mod n, in [0, n)
+__device__ __forceinline__ int wrap(int c, int n) {
+  c %= n;
+  return c < 0 ? c + n : c;
+}
+
+// The same for a c less than a period outside.
+__device__ __forceinline__ int wrap_near(int c, int n) { return c < 0 ? c + n : (c >= n ? c - n : c); }
+
+// With SKIP, the nodes [skip_x, skip_x + skip_w) x [skip_y, skip_y + skip_h),
+// wrapped, are left to another workgroup.
+struct SkipRect {
+  int x, y, w, h;
+};
+
+template <int ST, int FEAT, int PLM, int K, bool SKIP = false>
+__device__ __forceinline__ void multi_body(const DevDomain &D, typename Store<ST>::T (*lds)[region(K).cw * region(K).rs],
+                                           int tile, uint64_t T0, int nsteps,
+                                           SkipRect skip = SkipRect{}) {
   using S = Store<ST>;
   using T = typename S::T;
   using R = CompT<ST, 0>;
@@ -47,16 +72,11 @@ __device__ __forceinline__ void multi_body(const DevDomain &D, int tile, int kst
   constexpr int CW = G.cw, RS = G.rs, NT = G.nt, NODES = CW * RS, U = NODES / NT;
   static_assert(NODES % NT == 0, "whole nodes per thread");
   constexpr uint32_t B = sizeof(T);
-  __shared__ T lds[9][NODES];
 
   const int nx = D.nx, ny = D.ny, pitch = D.pitch;
   const int rim = nsteps - 1, ow = CW - 2 * rim, oh = RS - 2 * rim;
   const int tiles_x = (nx + ow - 1) / ow;
   const int ty = tile / tiles_x, tx = tile - ty * tiles_x;
-  // state time, made wave-uniform so that the buffers stay in scalar registers
-  const uint64_t ts = *gbl(D.tstep);
-  const uint64_t T0 = (((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(ts >> 32)) << 32) |
-                       __builtin_amdgcn_readfirstlane((uint32_t)ts)) + (uint64_t)kstep;
   const uint32_t pitchB = (uint32_t)pitch * B, planeB = (uint32_t)ny * pitchB;
   void *const f0 = D.f[0];
   void *const f1 = D.f[1];
@@ -66,18 +86,15 @@ __device__ __forceinline__ void multi_body(const DevDomain &D, int tile, int kst
   const bool sr = (ST == ST_F16 || ST == ST_BF16) && (D.feat & F_STOCH);
   bool bad = false;
 
-  auto wrap = [](int c, int n) {
-    c %= n;
-    return c < 0 ? c + n : c;
-  };
   // this thread's nodes: id = thread + u NT, row id / CW, column id % CW
   uint32_t w[U], node[U], here[U];
   int xu[U], yu[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int id = (int)threadIdx.x + u * NT;
-    xu[u] = wrap(tx * ow - rim + id % CW, nx);
-    yu[u] = wrap(ty * oh - rim + id / CW, ny);
+    const int x = tx * ow - rim + id % CW, y = ty * oh - rim + id / CW;
+    xu[u] = nx >= CW ? wrap_near(x, nx) : wrap(x, nx);
+    yu[u] = ny >= RS ? wrap_near(y, ny) : wrap(y, ny);
     w[u] = has_lab ? gbl(D.nodew)[(uint32_t)yu[u] * pitch + xu[u]] : 0u;
     node[u] = (uint32_t)yu[u] * (uint32_t)nx + (uint32_t)xu[u];
     here[u] = (uint32_t)yu[u] * pitchB + (uint32_t)xu[u] * B;
@@ -169,7 +186,9 @@ __device__ __forceinline__ void multi_body(const DevDomain &D, int tile, int kst
       collide_node<ST, FEAT, PLM, R>(D, e, node[u], step);
       if (s < nsteps)
         encode(e, node[u], step, [&](int i, T v) { lds[i][id] = v; });
-      else if (tx * ow + id % CW - rim < nx && ty * oh + id / CW - rim < ny)
+      else if (tx * ow + id % CW - rim < nx && ty * oh + id / CW - rim < ny &&
+               !(SKIP && (uint32_t)(xu[u] - skip.x + (xu[u] < skip.x ? nx : 0)) < (uint32_t)skip.w &&
+                 (uint32_t)(yu[u] - skip.y + (yu[u] < skip.y ? ny : 0)) < (uint32_t)skip.h))
         // ordinary stores: the lines that two tiles share merge in the cache
         encode(e, node[u], step,
                [&](int i, T v) { bstore<T, false>(dst, here[u], (uint32_t)i * planeB, v); });
@@ -183,18 +202,21 @@ __device__ __forceinline__ void multi_body(const DevDomain &D, int tile, int kst
 // 7 that a launch takes on a small lattice.
 template <int ST, int FEAT, int PLM, int K>
 __global__ __launch_bounds__(region(K).nt) void k_multi_one(const DevDomain D, int kstep, int nsteps) {
-  multi_body<ST, FEAT, PLM, K>(D, xcd_remap((int)blockIdx.x, (int)gridDim.x), kstep, nsteps);
+  __shared__ typename Store<ST>::T lds[9][region(K).cw * region(K).rs];
+  multi_body<ST, FEAT, PLM, K>(D, lds, xcd_remap((int)blockIdx.x, (int)gridDim.x),
+                               uniform_time(D, kstep), nsteps);
 }
 
 // The domains of a batch (prefix: tiles of nsteps-step launches per domain).
 template <int ST, int FEAT, int PLM, int K>
-__global__ __launch_bounds__(region(K).nt) void k_multi(const DevDomain *__restrict__ doms,
+__global__ __launch_bounds__(region(K).nt, 4) void k_multi(const DevDomain *__restrict__ doms,
                                                         const int *__restrict__ prefix, int ndom,
                                                         int kstep, int nsteps) {
+  __shared__ typename Store<ST>::T lds[9][region(K).cw * region(K).rs];
   const int b = xcd_remap((int)blockIdx.x, (int)gridDim.x);
   const int dix = ndom == 1 ? 0 : find_domain(prefix, ndom, b);
   const DevDomain D = doms[dix];  // held in scalar registers across the steps
-  multi_body<ST, FEAT, PLM, K>(D, ndom == 1 ? b : b - prefix[dix], kstep, nsteps);
+  multi_body<ST, FEAT, PLM, K>(D, lds, ndom == 1 ? b : b - prefix[dix], uniform_time(D, kstep), nsteps);
 }
 
 }  // namespace lbk
