@@ -22,12 +22,15 @@ void sweep_l(const DevDomain *doms, const int *prefix, int ndom, int kstep, int 
                      ndom, kstep, part);
 }
 template <int FEAT, int PLM>
-void multi_l(const DevDomain *doms, const int *prefix, int ndom, const DevDomain *one, int k,
-             int kstep, int nsteps, int blocks, hipStream_t s) {
-  if (k == 0 && one != nullptr) {
-    hipLaunchKernelGGL((k_multi_one<ST, FEAT, PLM, 0>), dim3(blocks), dim3(region(0).nt), 0, s, *one,
-                       kstep, nsteps);
-  } else if (k == 0) {
+void multi_one_l(const DevDomain *one, uint32_t *arrived, int kstep, int nsteps, int advance, int blocks,
+                 hipStream_t s) {
+  hipLaunchKernelGGL((k_multi_one<ST, FEAT, PLM, 0>), dim3(blocks), dim3(region(0).nt), 0, s, *one,
+                     arrived, kstep, nsteps, advance);
+}
+template <int FEAT, int PLM>
+void multi_l(const DevDomain *doms, const int *prefix, int ndom, int k, int kstep, int nsteps, int blocks,
+             hipStream_t s) {
+  if (k == 0) {
     hipLaunchKernelGGL((k_multi<ST, FEAT, PLM, 0>), dim3(blocks), dim3(region(0).nt), 0, s, doms,
                        prefix, ndom, kstep, nsteps);
   } else if (k == 1 || !region_fits(ST, 2)) {
@@ -94,11 +97,13 @@ template <int FEAT, int PLM, int WIDE> void fill(KernelSet *k) {
   k->sweep = sweep_l<FEAT, PLM, WIDE>;
   // several steps a launch: every set in native arithmetic but the power law
   // without a label plane or with noise
+  k->multi = nullptr;
+  k->multi_one = nullptr;
   if constexpr (WIDE == 0 && ((FEAT & F_POWER) == 0 ||
-                              ((FEAT & F_LABELS) != 0 && (FEAT & F_NOISE) == 0)))
+                              ((FEAT & F_LABELS) != 0 && (FEAT & F_NOISE) == 0))) {
     k->multi = multi_l<FEAT, PLM>;
-  else
-    k->multi = nullptr;
+    k->multi_one = multi_one_l<FEAT, PLM>;
+  }
   k->multi_disc = nullptr;
   if constexpr (WIDE == 0 && (FEAT & F_LABELS) != 0 && !((FEAT & F_POWER) != 0 && (FEAT & F_NOISE) != 0))
     k->multi_disc = multi_disc_l<FEAT, PLM>;

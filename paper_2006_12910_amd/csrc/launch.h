@@ -11,11 +11,15 @@ struct KernelSet {
   void (*sweep)(const DevDomain *doms, const int *prefix, int ndom, int kstep, int blocks, int part,
                 hipStream_t s);
   // `nsteps` steps (odd, 3 .. MULTI_MAX) per launch over `blocks` tiles of
-  // region k: the domains of `doms` (prefix: tiles per domain), or, where one
-  // is given, the single domain of descriptor `one` (region 0); null where
-  // the feature set has no such kernel
-  void (*multi)(const DevDomain *doms, const int *prefix, int ndom, const DevDomain *one, int k,
-                int kstep, int nsteps, int blocks, hipStream_t s);
+  // region k: the domains of `doms` (prefix: tiles per domain); null where the
+  // feature set has no such kernel
+  void (*multi)(const DevDomain *doms, const int *prefix, int ndom, int k, int kstep, int nsteps,
+                int blocks, hipStream_t s);
+  // the same (also 1 step) for the domain of descriptor `one` in region 0; with
+  // `advance` the launch also adds that to the step counter, through the
+  // zeroed counter `arrived`
+  void (*multi_one)(const DevDomain *one, uint32_t *arrived, int kstep, int nsteps, int advance,
+                    int blocks, hipStream_t s);
   // DISC_STEPS steps per launch of domains with at most one particle each, the
   // `nitems` particles of `items`, over `blocks` tiles of region
   // disc_region(storage); `one` the descriptor of a single domain or null; null where the feature set has no such kernel

@@ -52,7 +52,7 @@ struct Layout {
 struct Header {
   uint64_t tstep;
   uint32_t health;
-  uint32_t pad;
+  uint32_t arrived;  // workgroups of a launch that moves tstep on; zero between launches
   double mass;
   double mass_ctl[2];  // reference density sum, relative tolerance (0: off)
 };
@@ -389,6 +389,7 @@ struct StepPlan {
 struct MultiSteps {
   MultiPlan plan;
   const DevDomain *one = nullptr;         // the descriptor of a single domain
+  uint32_t *arrived = nullptr;            // and its counter of workgroups
   const lb_batch *batch = nullptr;        // or the batch
   bool disc = false;                      // with particles
   int tiles(int n) const { return batch ? batch->multi_tiles[n] : multi_tiles(plan.k, n, one->nx, one->ny); }
@@ -401,10 +402,17 @@ struct MultiSteps {
 // from a captured graph: a launch runs 7 us and more, longer than the host
 // takes to enqueue it, and captured chunks of fixed lengths would break the
 // calls into shorter launches (250 steps: 48 launches and 10 counter updates
-// instead of 36 and 1).
+// instead of 36 and 1).  With n_max 3, two single steps beside a part of 3 become
+// one of 5 (32 steps of 24 FP16 domains: ten launches of 3 and two of
+// 1, 2.65 ms; nine of 3 and one of 5, 2.57).
 //
 // With particles a launch takes DISC_STEPS, and a part of 1 is k_pre, the
 // sweep and k_post.
+//
+// A single domain of region 0 has its counter moved on by the last launch of
+// the call, if that has at most ADVANCE_BLOCKS workgroups.
+constexpr int ADVANCE_BLOCKS = 64;
+
 void disc_steps(const StepPlan &p, const DevDomain *one, const int *prefix, int tiles, int k, int len,
                 hipStream_t s) {
   if (len > 1) {
@@ -423,18 +431,29 @@ lb_status run_multi(const StepPlan &p, const MultiSteps &m, int64_t n, hipStream
     if ((parts ^ c) & 1) ++parts;
     int lo = c / parts;
     if (!(lo & 1)) --lo;
-    const int longer = (c - parts * lo) / 2;
+    int longer = (c - parts * lo) / 2, longest = 0;
+    if (!m.disc && lo == 1 && m.plan.nmax == 3) {
+      longest = std::min(longer, (parts - longer) / 2);
+      parts -= 2 * longest;
+      longer -= longest;
+    }
+    const bool one = m.one != nullptr && m.plan.k == 0 && !m.disc;
+    bool advanced = false;
     for (int i = 0, k = 0; i < parts; ++i) {
-      const int len = lo + (i < longer ? 2 : 0);
-      if (m.disc)
+      const int len = lo + (i < longest ? 4 : i < longest + longer ? 2 : 0);
+      if (one) {
+        const int tiles = m.tiles(len);
+        advanced = i + 1 == parts && tiles <= ADVANCE_BLOCKS;
+        p.ks->multi_one(m.one, m.arrived, k, len, advanced ? c : 0, tiles, s);
+      } else if (m.disc)
         disc_steps(p, m.one, m.prefix(len), m.tiles(len), k, len, s);
       else if (len > 1)
-        p.ks->multi(p.doms, m.prefix(len), p.ndom, m.one, m.plan.k, k, len, m.tiles(len), s);
+        p.ks->multi(p.doms, m.prefix(len), p.ndom, m.plan.k, k, len, m.tiles(len), s);
       else
         p.ks->sweep(p.doms, p.prefix, p.ndom, k, p.blocks, 0, s);
       k += len;
     }
-    launch_advance(p.doms, p.ndom, c, s);
+    if (!advanced) launch_advance(p.doms, p.ndom, c, s);
     HIPCHK(hipGetLastError());
     done += c;
   }
@@ -1086,6 +1105,7 @@ static lb_status lb_step_impl(lb_domain *d, int64_t nsteps) {
       MultiSteps m;
       m.plan = d->multi;
       m.one = &d->hd;
+      m.arrived = &d->dhdr()->arrived;
       s = run_multi(p, m, nsteps, d->stream);
     } else if (disc_ok(d) && !d->overlap && nsteps >= DISC_STEPS) {
       MultiSteps m;
@@ -1575,7 +1595,8 @@ static lb_status lb_batch_create_impl(lb_domain *const *domains, int32_t n, void
   b->multi_step = multi && !(b->disc && b->ks.multi_disc == nullptr);
   b->multi = b->disc ? disc_plan(domains[0]->desc.storage)
                      : choose_multi(domains[0]->desc.storage, feat, sizes);
-  for (int len = 3; len <= b->multi.nmax; len += 2) {
+  const int longest = b->multi.nmax == 3 ? 5 : b->multi.nmax;  // see run_multi
+  for (int len = 3; len <= longest; len += 2) {
     int *pre = prefix.data() + (size_t)(len + 1) / 2 * (n + 1);
     for (int i = 0; i < n; ++i)
       pre[i + 1] = pre[i] + multi_tiles(b->multi.k, len, sizes[i].first, sizes[i].second);

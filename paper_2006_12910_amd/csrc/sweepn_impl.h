@@ -60,7 +60,8 @@ struct SkipRect {
   int x, y, w, h;
 };
 
-template <int ST, int FEAT, int PLM, int K, bool SKIP = false>
+// ONE: a single step is possible, from global memory to global memory.
+template <int ST, int FEAT, int PLM, int K, bool SKIP = false, bool ONE = false>
 __device__ __forceinline__ void multi_body(const DevDomain &D, typename Store<ST>::T (*lds)[region(K).cw * region(K).rs],
                                            int tile, uint64_t T0, int nsteps,
                                            SkipRect skip = SkipRect{}) {
@@ -150,7 +151,11 @@ __device__ __forceinline__ void multi_body(const DevDomain &D, typename Store<ST
     bad = bad || !(fabs(scaled_drho<ST, R>(e)) < R(1e30));
     const uint32_t step = (uint32_t)(T0 + 1);
     collide_node<ST, FEAT, PLM, R>(D, e, node[u], step);
-    encode(e, node[u], step, [&](int i, T v) { lds[i][id] = v; });
+    if (!ONE || nsteps > 1)
+      encode(e, node[u], step, [&](int i, T v) { lds[i][id] = v; });
+    else if (tx * ow + id % CW < nx && ty * oh + id / CW < ny)
+      encode(e, node[u], step,
+             [&](int i, T v) { bstore<T, false>(dst, here[u], (uint32_t)i * planeB, v); });
   }
   // step s: the nodes at least s - 1 inside the region, from LDS, in place
 #pragma unroll 1
@@ -199,12 +204,31 @@ __device__ __forceinline__ void multi_body(const DevDomain &D, typename Store<ST
 
 // One domain, its descriptor in the kernel's arguments: without the load of
 // the descriptor the chain of dependent loads is one shorter, 0.6 us of the
-// 7 that a launch takes on a small lattice.
+// 7 that a launch takes on a small lattice.  A single step also comes here
+// (channel 128 x 64 FP64, 20 calls of one step and the moments: 125 -> 89 us).
+//
+// With `advance`, the launch is the last of its call and also moves the step
+// counter on, by the workgroup that arrives last at `arrived` (which it leaves
+// at zero): all have read the counter then.  It spares a launch of 2 us; a
+// workgroup's arrival is an atomic on one address for the whole device, so
+// only small grids do it.
 template <int ST, int FEAT, int PLM, int K>
-__global__ __launch_bounds__(region(K).nt) void k_multi_one(const DevDomain D, int kstep, int nsteps) {
+__global__ __launch_bounds__(region(K).nt) void k_multi_one(const DevDomain D, uint32_t *arrived,
+                                                            int kstep, int nsteps, int advance) {
   __shared__ typename Store<ST>::T lds[9][region(K).cw * region(K).rs];
-  multi_body<ST, FEAT, PLM, K>(D, lds, xcd_remap((int)blockIdx.x, (int)gridDim.x),
-                               uniform_time(D, kstep), nsteps);
+  const uint64_t T0 = uniform_time(D, kstep);
+  uint32_t place = 0;
+  if (advance) {
+    __syncthreads();
+    if (threadIdx.x == 0)
+      place = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  multi_body<ST, FEAT, PLM, K, false, true>(D, lds, xcd_remap((int)blockIdx.x, (int)gridDim.x), T0,
+                                            nsteps);
+  if (advance && threadIdx.x == 0 && place == gridDim.x - 1) {
+    *arrived = 0;
+    *D.tstep = T0 - (uint64_t)kstep + (uint64_t)advance;
+  }
 }
 
 // The domains of a batch (prefix: tiles of nsteps-step launches per domain).
