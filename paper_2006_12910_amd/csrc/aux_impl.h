@@ -76,36 +76,56 @@ __global__ __launch_bounds__(64) void k_mass_final(const DevDomain *__restrict__
 
 // rho and u = j/rho + g/2 of the pre-collision state f(T), recovered from
 // f*(T): collision keeps rho and adds rho g to j.  Band rows [row0, row0+nrows).
+//
+// Small domains are bound by the chain of dependent loads (4 us and up, and a
+// batch reads its members one after the other), large ones by the bytes (the
+// populations and 24 written a node).  The descriptor comes in the arguments,
+// the step counter and the labels are requested together, then the
+// populations of both of a thread's nodes, solid or not: FP32 4096^2 192 -> 183 us
+// (5.5 TB/s), 32 domains of 128^2 to 1024^2 7.0 -> 6.4 each, 24 FP16 ones of
+// 64^2 to 2048^2 10.9 -> 9.1.
 template <int ST>
-__global__ __launch_bounds__(256) void k_moments(const DevDomain *__restrict__ Dp, double *rho_o,
-                                                 double *ux_o, double *uy_o, int row0, int nrows) {
+__global__ __launch_bounds__(256) void k_moments(const DevDomain D, double *rho_o, double *ux_o,
+                                                 double *uy_o, int row0, int nrows) {
   using S = Store<ST>;
   using T = typename S::T;
-  const DevDomain &D = *Dp;
-  const long long n = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (n >= (long long)nrows * D.nx) return;
-  const int yl = (int)(n / D.nx), x = (int)(n - (long long)yl * D.nx);
-  const int y = row0 + yl;
-  if (node_is_solid(D, x, y)) {
-    rho_o[n] = 0.0; ux_o[n] = 0.0; uy_o[n] = 0.0;
-    return;
-  }
-  const uint64_t T0 = *D.tstep;
-  const T *src = (const T *)D.f[T0 & 1];
-  const size_t plane = (size_t)D.ny * D.pitch;
-  const uint32_t here = (uint32_t)y * D.pitch + x;
-  double dr = 0.0, jx = 0.0, jy = 0.0;
+  constexpr int U = 2;
+  const uint32_t count = (uint32_t)nrows * (uint32_t)D.nx;
+  uint32_t n[U], here[U];
+  bool solid[U];
 #pragma unroll
-  for (int i = 0; i < 9; ++i) {
-    const double v = (double)S::load(src + i * plane, here, i);
-    dr += v;
-    jx += v * cx(i);
-    jy += v * cy(i);
+  for (int u = 0; u < U; ++u) {
+    n[u] = blockIdx.x * (U * 256u) + u * 256u + threadIdx.x;
+    const uint32_t m = min(n[u], count - 1u);
+    const uint32_t yl = m / (uint32_t)D.nx, x = m - yl * (uint32_t)D.nx;
+    here[u] = ((uint32_t)row0 + yl) * D.pitch + x;
+    solid[u] = node_is_solid(D, (int)x, row0 + (int)yl);
   }
-  const double rho = D.rho0 + dr;
-  rho_o[n] = rho;
-  ux_o[n] = jx / rho - 0.5 * D.gx;
-  uy_o[n] = jy / rho - 0.5 * D.gy;
+  void *const f0 = D.f[0];
+  void *const f1 = D.f[1];
+  const T *src = (const T *)((*gbl(D.tstep) & 1) ? f1 : f0);
+  const size_t plane = (size_t)D.ny * D.pitch;
+  T v[U][9];
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+#pragma unroll
+    for (int i = 0; i < 9; ++i) v[u][i] = gbl(src + i * plane)[here[u]];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if (n[u] >= count) continue;
+    double dr = 0.0, jx = 0.0, jy = 0.0;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+      const double f = (double)S::dec(v[u][i], i);
+      dr += f;
+      if (cx(i) != 0) jx += cx(i) > 0 ? f : -f;
+      if (cy(i) != 0) jy += cy(i) > 0 ? f : -f;
+    }
+    const double rho = D.rho0 + dr;
+    rho_o[n[u]] = solid[u] ? 0.0 : rho;
+    ux_o[n[u]] = solid[u] ? 0.0 : jx / rho - 0.5 * D.gx;
+    uy_o[n[u]] = solid[u] ? 0.0 : jy / rho - 0.5 * D.gy;
+  }
 }
 
 // Mirror slots of the index walls of a label-free domain in the current

@@ -70,11 +70,11 @@ void mass_l(const DevDomain *doms, const int *prefix, int ndom, int blocks, doub
             hipStream_t s) {
   hipLaunchKernelGGL((k_mass_partial<ST>), dim3(blocks), dim3(256), 0, s, doms, prefix, ndom, alt);
 }
-void moments_l(const DevDomain *dom, double *rho, double *ux, double *uy, int row0, int nrows,
-               int nx, hipStream_t s) {
-  const long long n = (long long)nrows * nx;
-  hipLaunchKernelGGL((k_moments<ST>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, dom,
-                     rho, ux, uy, row0, nrows);
+void moments_l(const DevDomain &dom, double *rho, double *ux, double *uy, int row0, int nrows,
+               hipStream_t s) {
+  const long long n = (long long)nrows * dom.nx;
+  hipLaunchKernelGGL((k_moments<ST>), dim3((unsigned)((n + 511) / 512)), dim3(256), 0, s, dom, rho, ux,
+                     uy, row0, nrows);
 }
 void export_l(const DevDomain *dom, double *out, int row0, int nrows, int nx, hipStream_t s) {
   const long long n = (long long)nrows * nx;

@@ -38,8 +38,8 @@ struct KernelSet {
   // into each domain's partials, or into alt (one domain)
   void (*mass_partial)(const DevDomain *doms, const int *prefix, int ndom, int blocks,
                        double *alt, hipStream_t s);
-  void (*moments)(const DevDomain *dom, double *rho, double *ux, double *uy, int row0, int nrows,
-                  int nx, hipStream_t s);
+  void (*moments)(const DevDomain &dom, double *rho, double *ux, double *uy, int row0, int nrows,
+                  hipStream_t s);
   void (*export_f)(const DevDomain *dom, double *out, int row0, int nrows, int nx, hipStream_t s);
   void (*import_f)(const DevDomain *dom, const double *in, int row0, int nrows, int nx,
                    hipStream_t s);

@@ -1129,7 +1129,7 @@ lb_status lb_step(lb_domain *d, int64_t nsteps) {
 
 static lb_status lb_moments_device_impl(lb_domain *d, double *rho, double *ux, double *uy) {
   if (!d || !rho || !ux || !uy) return fail(LB_EINVAL, "null argument");
-  d->ks.moments(d->ddesc(), rho, ux, uy, 0, d->desc.ny, d->desc.nx, d->stream);
+  d->ks.moments(d->hd, rho, ux, uy, 0, d->desc.ny, d->stream);
   HIPCHK(hipGetLastError());
   return LB_OK;
 }
@@ -1151,7 +1151,7 @@ static lb_status lb_moments_async_impl(lb_domain *d, double *dev_stage, double *
   const size_t cnt = (size_t)nx * ny;
   // the staging memory of an earlier call may still be being copied out
   if (d->rep_pending) HIPCHK(hipStreamWaitEvent(d->stream, d->rep_copied, 0));
-  d->ks.moments(d->ddesc(), dev_stage, dev_stage + cnt, dev_stage + 2 * cnt, 0, ny, nx, d->stream);
+  d->ks.moments(d->hd, dev_stage, dev_stage + cnt, dev_stage + 2 * cnt, 0, ny, d->stream);
   HIPCHK(hipGetLastError());
   HIPCHK(hipEventRecord(d->rep_ready, d->stream));
   HIPCHK(hipStreamWaitEvent(cs, d->rep_ready, 0));
@@ -1188,7 +1188,7 @@ static lb_status lb_moments_impl(lb_domain *d, double *rho, double *ux, double *
   for (int r0 = 0; r0 < d->desc.ny; r0 += d->L.band_rows) {
     const int nr = std::min(d->L.band_rows, d->desc.ny - r0);
     const size_t cnt = (size_t)nr * nx;
-    d->ks.moments(d->ddesc(), st, st + cnt, st + 2 * cnt, r0, nr, nx, d->stream);
+    d->ks.moments(d->hd, st, st + cnt, st + 2 * cnt, r0, nr, d->stream);
     HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(rho + (size_t)r0 * nx, st, cnt * 8, hipMemcpyDeviceToHost, d->stream));
     HIPCHK(hipMemcpyAsync(ux + (size_t)r0 * nx, st + cnt, cnt * 8, hipMemcpyDeviceToHost, d->stream));
