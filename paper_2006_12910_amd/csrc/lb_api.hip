@@ -406,23 +406,15 @@ struct MultiSteps {
 // one of 5 (32 steps of 24 FP16 domains: ten launches of 3 and two of
 // 1, 2.65 ms; nine of 3 and one of 5, 2.57).
 //
-// With particles a launch takes DISC_STEPS, and a part of 1 is k_pre, the
-// sweep and k_post.
+// With particles a launch takes DISC_STEPS; single steps, the last of the call,
+// are k_pre, the sweep and k_post, with the post pass of one and the pre pass of
+// the next in one launch.  They are not replayed from a graph either: a call of
+// one step takes the same 40 us at 475 x 363, and the first is spared the 0.9 ms
+// of the captures.
 //
 // A single domain of region 0 has its counter moved on by the last launch of
 // the call, if that has at most ADVANCE_BLOCKS workgroups.
 constexpr int ADVANCE_BLOCKS = 64;
-
-void disc_steps(const StepPlan &p, const DevDomain *one, const int *prefix, int tiles, int k, int len,
-                hipStream_t s) {
-  if (len > 1) {
-    p.ks->multi_disc(p.doms, prefix, p.ndom, p.items, p.nitems, one, k, tiles, s);
-    return;
-  }
-  p.ks->pre(p.doms, p.items, p.nitems, k, s);
-  p.ks->sweep(p.doms, p.prefix, p.ndom, k, p.blocks, 0, s);
-  p.ks->post(p.doms, p.items, p.nitems, k, s);
-}
 
 lb_status run_multi(const StepPlan &p, const MultiSteps &m, int64_t n, hipStream_t s) {
   for (int64_t done = 0; done < n;) {
@@ -445,9 +437,14 @@ lb_status run_multi(const StepPlan &p, const MultiSteps &m, int64_t n, hipStream
         const int tiles = m.tiles(len);
         advanced = i + 1 == parts && tiles <= ADVANCE_BLOCKS;
         p.ks->multi_one(m.one, m.arrived, k, len, advanced ? c : 0, tiles, s);
-      } else if (m.disc)
-        disc_steps(p, m.one, m.prefix(len), m.tiles(len), k, len, s);
-      else if (len > 1)
+      } else if (m.disc && len > 1) {
+        p.ks->multi_disc(p.doms, m.prefix(len), p.ndom, p.items, p.nitems, m.one, k, m.tiles(len), s);
+      } else if (m.disc) {
+        if (i == longer) p.ks->pre(p.doms, p.items, p.nitems, k, s);
+        p.ks->sweep(p.doms, p.prefix, p.ndom, k, p.blocks, 0, s);
+        if (i + 1 < parts) p.ks->post_pre(p.doms, p.items, p.nitems, k, s);
+        else p.ks->post(p.doms, p.items, p.nitems, k, s);
+      } else if (len > 1)
         p.ks->multi(p.doms, m.prefix(len), p.ndom, m.plan.k, k, len, m.tiles(len), s);
       else
         p.ks->sweep(p.doms, p.prefix, p.ndom, k, p.blocks, 0, s);
@@ -1107,7 +1104,7 @@ static lb_status lb_step_impl(lb_domain *d, int64_t nsteps) {
       m.one = &d->hd;
       m.arrived = &d->dhdr()->arrived;
       s = run_multi(p, m, nsteps, d->stream);
-    } else if (disc_ok(d) && !d->overlap && nsteps >= DISC_STEPS) {
+    } else if (disc_ok(d) && !d->overlap) {
       MultiSteps m;
       m.plan = disc_plan(d->desc.storage);
       m.one = &d->hd;
@@ -1647,7 +1644,7 @@ static lb_status lb_batch_step_impl(lb_batch *b, int64_t nsteps) {
     p.fuse_pp = true;
     for (auto *m : b->doms) p.fuse_pp = p.fuse_pp && m->np <= 1;
     lb_status s;
-    if (b->multi_step && (!b->disc || nsteps >= DISC_STEPS)) {
+    if (b->multi_step) {
       MultiSteps m;
       m.plan = b->multi;
       m.batch = b;
