@@ -24,6 +24,8 @@ CASES = [  # nx, ny, storage, domain arguments, disc
     (257, 129, "f32", dict(lj=(1e-3, 2.5, 0.5), solids=True, **NOISE),
      dict(x=128.5, y=64.5, radius=6.5, ux=-0.3, uy=0.3, favg=True)),
     (128, 96, "f32", dict(), dict(x=64.0, y=48.0, radius=3.0, fixed=True, omega=0.02)),
+    # beside a wall: the particle's region reaches past it to the far side
+    (96, 60, "f32", dict(lj=(1e-3, 2.5, 0.5), walls=True, **NOISE), dict(x=3.0, y=5.5, radius=3.0, ux=0.1)),
     # single steps in both: too small a domain, too large a disc
     (31, 40, "f32", NOISE, dict(x=20.0, y=20.0, radius=5.0, ux=0.2)),
     (128, 96, "f32", NOISE, dict(x=64.0, y=48.0, radius=8.2, ux=0.2)),
