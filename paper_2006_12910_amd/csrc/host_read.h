@@ -30,7 +30,32 @@ struct HostRing {
   static constexpr size_t SLOT_BYTES = size_t(4) << 20;
   char *mem[SLOTS] = {};
   hipEvent_t ev[SLOTS] = {};
-  bool ready() {  // false: no pinned memory; the caller copies without it
+  // false: no pinned memory; the caller copies without it.  The events belong
+  // to the stream's device, whichever is current.
+  bool ready(hipStream_t s) {
+    if (ev[SLOTS - 1]) return true;
+    int current = 0, device = 0;
+    if (hipGetDevice(&current) != hipSuccess || hipStreamGetDevice(s, &device) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    if (device != current && hipSetDevice(device) != hipSuccess) return false;
+    const bool ok = make();
+    if (device != current) (void)hipSetDevice(current);
+    return ok;
+  }
+  HostRing() = default;
+  HostRing(const HostRing &) = delete;
+  HostRing &operator=(const HostRing &) = delete;
+  ~HostRing() {
+    for (int i = 0; i < SLOTS; ++i) {
+      if (ev[i]) (void)hipEventDestroy(ev[i]);
+      if (mem[i]) (void)hipHostFree(mem[i]);
+    }
+  }
+
+ private:
+  bool make() {
     for (int i = 0; i < SLOTS; ++i) {
       if (!mem[i] && hipHostMalloc((void **)&mem[i], SLOT_BYTES, hipHostMallocDefault) != hipSuccess) {
         mem[i] = nullptr;
@@ -44,15 +69,6 @@ struct HostRing {
       }
     }
     return true;
-  }
-  HostRing() = default;
-  HostRing(const HostRing &) = delete;
-  HostRing &operator=(const HostRing &) = delete;
-  ~HostRing() {
-    for (int i = 0; i < SLOTS; ++i) {
-      if (ev[i]) (void)hipEventDestroy(ev[i]);
-      if (mem[i]) (void)hipHostFree(mem[i]);
-    }
   }
 };
 
@@ -164,7 +180,7 @@ template <class Launch>
 hipError_t read_fields(HostRing &ring, double *const *h, int planes, long long n, double *stage,
                        long long max_cnt, hipStream_t s, Launch launch) {
   hipError_t e = hipSuccess;
-  if ((size_t)n * planes * 8 < HOST_RING_MIN_BYTES || !ring.ready()) {
+  if ((size_t)n * planes * 8 < HOST_RING_MIN_BYTES || !ring.ready(s)) {
     for (long long n0 = 0; n0 < n; n0 += max_cnt) {
       const long long cnt = std::min(max_cnt, n - n0);
       launch(n0, cnt);

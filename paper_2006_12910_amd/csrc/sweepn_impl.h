@@ -87,13 +87,18 @@ __device__ __forceinline__ void multi_body(const DevDomain &D, typename Store<ST
   const bool sr = (ST == ST_F16 || ST == ST_BF16) && (D.feat & F_STOCH);
   bool bad = false;
 
-  // this thread's nodes: id = thread + u NT, row id / CW, column id % CW
+  // this thread's nodes: id = thread + u NT, row id / CW, column id % CW.  Where
+  // a wave is one row, the row and its addresses live in scalar registers.
+  static_assert(NT % CW == 0, "the same column in every row");
+  const int col = (int)threadIdx.x % CW;
+  const int row0 = CW == 64 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / CW)
+                            : (int)threadIdx.x / CW;
+  constexpr int RSTEP = NT / CW;
   uint32_t w[U], node[U], here[U];
   int xu[U], yu[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const int id = (int)threadIdx.x + u * NT;
-    const int x = tx * ow - rim + id % CW, y = ty * oh - rim + id / CW;
+    const int x = tx * ow - rim + col, y = ty * oh - rim + row0 + u * RSTEP;
     xu[u] = nx >= CW ? wrap_near(x, nx) : wrap(x, nx);
     yu[u] = ny >= RS ? wrap_near(y, ny) : wrap(y, ny);
     w[u] = has_lab ? gbl(D.nodew)[(uint32_t)yu[u] * pitch + xu[u]] : 0u;
@@ -153,7 +158,7 @@ __device__ __forceinline__ void multi_body(const DevDomain &D, typename Store<ST
     collide_node<ST, FEAT, PLM, R>(D, e, node[u], step);
     if (!ONE || nsteps > 1)
       encode(e, node[u], step, [&](int i, T v) { lds[i][id] = v; });
-    else if (tx * ow + id % CW < nx && ty * oh + id / CW < ny)
+    else if (tx * ow + col < nx && ty * oh + row0 + u * RSTEP < ny)
       encode(e, node[u], step,
              [&](int i, T v) { bstore<T, false>(dst, here[u], (uint32_t)i * planeB, v); });
   }
@@ -166,8 +171,8 @@ __device__ __forceinline__ void multi_body(const DevDomain &D, typename Store<ST
     bool act[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int id = (int)threadIdx.x + u * NT, r = id / CW, c = id % CW;
-      act[u] = r >= m && r < RS - m && c >= m && c < CW - m;
+      const int id = (int)threadIdx.x + u * NT, r = row0 + u * RSTEP;
+      act[u] = r >= m && r < RS - m && col >= m && col < CW - m;
       if (!act[u]) continue;
       const T *p = &lds[0][0] + id;
       raw[u].set(0, p[0]);
@@ -191,7 +196,7 @@ __device__ __forceinline__ void multi_body(const DevDomain &D, typename Store<ST
       collide_node<ST, FEAT, PLM, R>(D, e, node[u], step);
       if (s < nsteps)
         encode(e, node[u], step, [&](int i, T v) { lds[i][id] = v; });
-      else if (tx * ow + id % CW - rim < nx && ty * oh + id / CW - rim < ny &&
+      else if (tx * ow + col - rim < nx && ty * oh + row0 + u * RSTEP - rim < ny &&
                !(SKIP && (uint32_t)(xu[u] - skip.x + (xu[u] < skip.x ? nx : 0)) < (uint32_t)skip.w &&
                  (uint32_t)(yu[u] - skip.y + (yu[u] < skip.y ? ny : 0)) < (uint32_t)skip.h))
         // ordinary stores: the lines that two tiles share merge in the cache
