@@ -355,7 +355,7 @@ __global__ __launch_bounds__(region(K).nt, 4) void k_multi_disc(const DevDomain 
   if (one.nx > 0) D = one;
   else D = doms[dix];
   const uint64_t T0 = uniform_time(D, kstep);
-  multi_body<ST, FEAT, PLM, K, true>(D, *(Tile *)mem, ndom == 1 ? b : b - prefix[dix], T0, DISC_STEPS,
+  multi_body<ST, FEAT, PLM, K, region(K).nt, true>(D, *(Tile *)mem, ndom == 1 ? b : b - prefix[dix], T0, DISC_STEPS,
                                      D.np > 0 ? disc_rect(D, T0) : SkipRect{0, 0, 0, 0});
 }
 

@@ -31,14 +31,14 @@ template <int FEAT, int PLM>
 void multi_l(const DevDomain *doms, const int *prefix, int ndom, int k, int kstep, int nsteps, int blocks,
              hipStream_t s) {
   if (k == 0) {
-    hipLaunchKernelGGL((k_multi<ST, FEAT, PLM, 0>), dim3(blocks), dim3(region(0).nt), 0, s, doms,
+    hipLaunchKernelGGL((k_multi<ST, FEAT, PLM, 0>), dim3(blocks), dim3(multi_threads(ST, 0, FEAT)), 0, s, doms,
                        prefix, ndom, kstep, nsteps);
   } else if (k == 1 || !region_fits(ST, 2)) {
-    hipLaunchKernelGGL((k_multi<ST, FEAT, PLM, 1>), dim3(blocks), dim3(region(1).nt), 0, s, doms,
+    hipLaunchKernelGGL((k_multi<ST, FEAT, PLM, 1>), dim3(blocks), dim3(multi_threads(ST, 1, FEAT)), 0, s, doms,
                        prefix, ndom, kstep, nsteps);
   } else {
     if constexpr (region_fits(ST, 2))
-      hipLaunchKernelGGL((k_multi<ST, FEAT, PLM, 2>), dim3(blocks), dim3(region(2).nt), 0, s, doms,
+      hipLaunchKernelGGL((k_multi<ST, FEAT, PLM, 2>), dim3(blocks), dim3(multi_threads(ST, 2, FEAT)), 0, s, doms,
                          prefix, ndom, kstep, nsteps);
   }
 }

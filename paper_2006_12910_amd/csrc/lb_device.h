@@ -73,6 +73,20 @@ __host__ __device__ constexpr Region region(int k) {
 }
 // the large region of 8-byte values would take 147 KB of LDS
 constexpr bool region_fits(int storage, int k) { return !(storage == ST_F64 && k == 2); }
+// Threads per region.  FP16 domains with labels take a thread per two nodes of
+// the large one: 64 registers, so two workgroups of 16 waves a CU, all that it
+// can hold (a thread per four: 106 registers, 16 waves).  Us a step, before and
+// after: 20 % obstacles 900 x 700 4.75 -> 4.18, 1448^2 11.6 -> 11.8, 4096^2 81.0 ->
+// 72.2; 24 uneven domains, 32 steps, 2.52 -> 2.34 ms.  Without labels the same
+// form is bound by memory and slower on large lattices (4096^2 54.5 -> 61.9).
+// FP32 and BF16 do not fit 64 registers without spills (201 domains of 64^2 to
+// 8192^2, ms a step: 0.861 -> 1.342, 0.889 -> 0.961); noise and the power law
+// take more still.
+__host__ __device__ constexpr int multi_threads(int storage, int k, int feat) {
+  return k == 2 && storage == ST_F16 && (feat & (F_LABELS | F_NOISE | F_POWER)) == F_LABELS
+             ? 1024
+             : region(k).nt;
+}
 constexpr int MULTI_MAX = 9;  // most steps a launch takes
 
 // Steps per launch of domains with one particle (discn_impl.h), the tiles'

@@ -61,8 +61,9 @@ struct SkipRect {
 };
 
 // ONE: a single step is possible, from global memory to global memory.
-template <int ST, int FEAT, int PLM, int K, bool SKIP = false, bool ONE = false>
-__device__ __forceinline__ void multi_body(const DevDomain &D, typename Store<ST>::T (*lds)[region(K).cw * region(K).rs],
+template <int ST, int FEAT, int PLM, int K, int NT, bool SKIP = false, bool ONE = false>
+__device__ __forceinline__ void multi_body(const DevDomain &D,
+                                           typename Store<ST>::T (*lds)[region(K).cw * region(K).rs],
                                            int tile, uint64_t T0, int nsteps,
                                            SkipRect skip = SkipRect{}) {
   using S = Store<ST>;
@@ -70,7 +71,7 @@ __device__ __forceinline__ void multi_body(const DevDomain &D, typename Store<ST
   using R = CompT<ST, 0>;
   constexpr bool LABELS = (FEAT & F_LABELS) != 0;
   constexpr Region G = region(K);
-  constexpr int CW = G.cw, RS = G.rs, NT = G.nt, NODES = CW * RS, U = NODES / NT;
+  constexpr int CW = G.cw, RS = G.rs, NODES = CW * RS, U = NODES / NT;
   static_assert(NODES % NT == 0, "whole nodes per thread");
   constexpr uint32_t B = sizeof(T);
 
@@ -228,7 +229,7 @@ __global__ __launch_bounds__(region(K).nt) void k_multi_one(const DevDomain D, u
     if (threadIdx.x == 0)
       place = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  multi_body<ST, FEAT, PLM, K, false, true>(D, lds, xcd_remap((int)blockIdx.x, (int)gridDim.x), T0,
+  multi_body<ST, FEAT, PLM, K, region(K).nt, false, true>(D, lds, xcd_remap((int)blockIdx.x, (int)gridDim.x), T0,
                                             nsteps);
   if (advance && threadIdx.x == 0 && place == gridDim.x - 1) {
     *arrived = 0;
@@ -238,14 +239,14 @@ __global__ __launch_bounds__(region(K).nt) void k_multi_one(const DevDomain D, u
 
 // The domains of a batch (prefix: tiles of nsteps-step launches per domain).
 template <int ST, int FEAT, int PLM, int K>
-__global__ __launch_bounds__(region(K).nt, 4) void k_multi(const DevDomain *__restrict__ doms,
-                                                        const int *__restrict__ prefix, int ndom,
-                                                        int kstep, int nsteps) {
+__global__ __launch_bounds__(multi_threads(ST, K, FEAT), multi_threads(ST, K, FEAT) / 128) void k_multi(
+    const DevDomain *__restrict__ doms, const int *__restrict__ prefix, int ndom, int kstep, int nsteps) {
   __shared__ typename Store<ST>::T lds[9][region(K).cw * region(K).rs];
   const int b = xcd_remap((int)blockIdx.x, (int)gridDim.x);
   const int dix = ndom == 1 ? 0 : find_domain(prefix, ndom, b);
   const DevDomain D = doms[dix];  // held in scalar registers across the steps
-  multi_body<ST, FEAT, PLM, K>(D, lds, ndom == 1 ? b : b - prefix[dix], uniform_time(D, kstep), nsteps);
+  multi_body<ST, FEAT, PLM, K, multi_threads(ST, K, FEAT)>(
+      D, lds, ndom == 1 ? b : b - prefix[dix], uniform_time(D, kstep), nsteps);
 }
 
 }  // namespace lbk
