@@ -165,7 +165,7 @@ __global__ __launch_bounds__(256) void k_export(const DevDomain *__restrict__ Dp
   const T *src = (const T *)D.f[T0 & 1];
   const size_t plane = (size_t)D.ny * D.pitch;
   const uint32_t here = (uint32_t)(row0 + yl) * D.pitch + x;
-  const bool solid = node_is_solid(D, x, row0 + yl);  // never written by the sweep
+  const bool solid = node_is_solid(D, x, row0 + yl);  // at rest, whatever it holds
   for (int i = 0; i < 9; ++i)
     out[(size_t)i * nrows * D.nx + n] = solid ? 0.0 : (double)S::load(src + i * plane, here, i);
 }

@@ -146,15 +146,20 @@ __device__ __forceinline__ void multi_body(const DevDomain &D,
       for (int i = 0; i < 9; ++i) put(i, q[i]);
     }
   };
-  // A solid node's first-step values are never read (a pull from it bounces
-  // back), so it collides whatever it pulled; later it is swept at rest.
+  // A solid node is swept at rest, as in k_sweep, wherever its values are
+  // stored to memory: a solid neighbour's next pull would read them.  The first
+  // of several steps is only kept in LDS, where nothing reads them (a pull from
+  // a solid bounces back), so there it collides whatever it pulled; in either
+  // case what a solid holds is not checked.
+  const bool stored = ONE && nsteps == 1;
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int id = (int)threadIdx.x + u * NT;
+    const bool solid = LABELS && (w[u] & NODE_SOLID);
     R e[9];
 #pragma unroll
-    for (int i = 0; i < 9; ++i) e[i] = (R)S::raw_dec(raw[u].get(i));
-    bad = bad || !(fabs(scaled_drho<ST, R>(e)) < R(1e30));
+    for (int i = 0; i < 9; ++i) e[i] = stored && solid ? R(0) : (R)S::raw_dec(raw[u].get(i));
+    bad = bad || (!solid && !(fabs(scaled_drho<ST, R>(e)) < R(1e30)));
     const uint32_t step = (uint32_t)(T0 + 1);
     collide_node<ST, FEAT, PLM, R>(D, e, node[u], step);
     if (!ONE || nsteps > 1)
