@@ -57,6 +57,8 @@ void init_l(const DevDomain *dom, const double *rho, const double *ux, const dou
   hipLaunchKernelGGL((k_init<ST, FEAT, PLM, WIDE>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
                      dom, rho, ux, uy, row0, nrows);
 }
+
+#ifndef LBK_GENERIC_POWER_FILE
 void pre_l(const DevDomain *doms, const PItem *items, int nitems, int kstep, hipStream_t s) {
   hipLaunchKernelGGL((k_pre<ST>), dim3(nitems), dim3(PT), 0, s, doms, items, kstep);
 }
@@ -92,8 +94,10 @@ void mirror_l(const DevDomain *dom, int nx, int ny, hipStream_t s) {
   const long long n = (long long)nx * ny;
   hipLaunchKernelGGL((k_mirror<ST>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, dom);
 }
+#endif
 
-template <int FEAT, int PLM, int WIDE> void fill(KernelSet *k) {
+// The kernels that collide.
+template <int FEAT, int PLM, int WIDE> void fill_steps(KernelSet *k) {
   k->sweep = sweep_l<FEAT, PLM, WIDE>;
   // several steps a launch: every set in native arithmetic but the power law
   // without a label plane or with noise
@@ -108,6 +112,11 @@ template <int FEAT, int PLM, int WIDE> void fill(KernelSet *k) {
   if constexpr (WIDE == 0 && (FEAT & F_LABELS) != 0 && !((FEAT & F_POWER) != 0 && (FEAT & F_NOISE) != 0))
     k->multi_disc = multi_disc_l<FEAT, PLM>;
   k->init = init_l<FEAT, PLM, WIDE>;
+}
+
+#ifndef LBK_GENERIC_POWER_FILE
+
+void fill_rest(KernelSet *k) {
   k->pre = pre_l;
   k->post = post_l;
   k->post_pre = post_pre_l;
@@ -118,10 +127,19 @@ template <int FEAT, int PLM, int WIDE> void fill(KernelSet *k) {
   k->mirror = mirror_l;
 }
 
+template <int FEAT, int PLM, int WIDE> void fill(KernelSet *k) {
+  fill_steps<FEAT, PLM, WIDE>(k);
+  fill_rest(k);
+}
+
 template <int BASE, int WIDE> bool pick_power(int feat, int plm, KernelSet *k) {
   if (!(feat & F_POWER)) { fill<BASE, PL_GENERIC, WIDE>(k); return true; }
   switch (plm) {
+#ifdef LBK_GENERIC_POWER
+    case PL_GENERIC: fill_rest(k); return LBK_GENERIC_POWER(feat, k);
+#else
     case PL_GENERIC: fill<BASE | F_POWER, PL_GENERIC, WIDE>(k); return true;
+#endif
     case PL_HALF: fill<BASE | F_POWER, PL_HALF, WIDE>(k); return true;
     case PL_3Q: fill<BASE | F_POWER, PL_3Q, WIDE>(k); return true;
     case PL_3H: fill<BASE | F_POWER, PL_3H, WIDE>(k); return true;
@@ -141,11 +159,28 @@ template <int WIDE> bool pick(int feat, int plm, KernelSet *k) {
   return false;  // TRT with noise is refused at validation
 }
 
+#endif  // LBK_GENERIC_POWER_FILE
+
 }  // namespace
 
+#ifndef LBK_GENERIC_POWER_FILE
 bool LBK_GETTER(int feat, int plm, int wide, KernelSet *k) {
   if (ST == ST_F64 || !wide) return pick<0>(feat, plm, k);
   return pick<1>(feat, plm, k);
 }
+#else
+// The kernels that collide with the power law of any exponent.
+bool LBK_GETTER(int feat, KernelSet *k) {
+  switch (feat & (F_LABELS | F_NOISE | F_TRT)) {
+    case 0: fill_steps<F_POWER, PL_GENERIC, 0>(k); return true;
+    case F_LABELS: fill_steps<F_POWER | F_LABELS, PL_GENERIC, 0>(k); return true;
+    case F_NOISE: fill_steps<F_POWER | F_NOISE, PL_GENERIC, 0>(k); return true;
+    case F_LABELS | F_NOISE: fill_steps<F_POWER | F_LABELS | F_NOISE, PL_GENERIC, 0>(k); return true;
+    case F_TRT: fill_steps<F_POWER | F_TRT, PL_GENERIC, 0>(k); return true;
+    case F_LABELS | F_TRT: fill_steps<F_POWER | F_LABELS | F_TRT, PL_GENERIC, 0>(k); return true;
+  }
+  return false;
+}
+#endif
 
 }  // namespace lbk

@@ -49,6 +49,7 @@ struct KernelSet {
 // Kernel set of a storage format / feature set / power-law specialisation /
 // arithmetic width (wide = FP64 arithmetic with any storage).
 bool kernels_f64(int feat, int plm, int wide, KernelSet *k);
+bool kernels_f64_pow(int feat, KernelSet *k);  // only the kernels that collide, any exponent
 bool kernels_f32(int feat, int plm, int wide, KernelSet *k);
 bool kernels_f16(int feat, int plm, int wide, KernelSet *k);
 bool kernels_bf16(int feat, int plm, int wide, KernelSet *k);

@@ -1,0 +1,58 @@
+"""Several steps a launch against single steps (LB_OPT_TWO_STEP off), by the
+clock: on lattices that fill the GPU, where neither launches nor rounding
+counts for much, the plan that the library takes by itself is not slower than
+the single steps it stands in for.  The bound leaves 15 % for the clock; the
+faults that these cases stand for cost 20 to 60 %."""
+import time
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _domain(lb, nx, ny, storage, kw, two, disc):
+    kw = dict(kw)
+    if kw.pop("obstacles", False):
+        kw["obstacles"] = np.random.default_rng(1).random((ny, nx)) < 0.05
+    y, x = np.arange(ny)[:, None], np.arange(nx)[None, :]
+    init = (1.0, 0.02 * np.sin(2 * np.pi * 3 * y / ny + 0.3) + 0 * x, 0.01 * np.cos(4 * np.pi * x / nx) + 0 * y)
+    d = lb.Domain(nx, ny, tau=0.8, storage=storage, seed=7, init=init, max_particles=1 if disc else 0,
+                  rounding="stochastic" if storage in ("f16", "bf16") else "nearest", **kw)
+    d.set_option(lb.OPT_TWO_STEP, two)
+    if disc:
+        d.add_particles([dict(x=nx / 2, y=ny / 2, radius=5.0, density_ratio=1.5)])
+    return d
+
+
+def _times(doms, n):
+    """Best time of a call of n steps, the domains in turn."""
+    import torch
+    best = [1e9] * len(doms)
+    for rep in range(9):
+        for i, d in enumerate(doms):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(4):
+                d.step(n)
+            torch.cuda.synchronize()
+            if rep:
+                best[i] = min(best[i], time.perf_counter() - t0)
+    return best
+
+
+POWER = lambda n: dict(bc_y="wall", power_law=dict(n=n, K=0.01))
+
+
+@pytest.mark.parametrize("storage,kw,nx,ny,n,disc", [
+    ("f64", POWER(1.3), 2048, 2048, 30, False),  # the generic exponent's pow: registers
+    ("f64", POWER(1.3), 2048, 1024, 8, False),
+    ("f64", POWER(1.3), 2048, 2048, 6, True),
+])
+def test_several_steps_a_launch_are_not_slower_than_single_ones(storage, kw, nx, ny, n, disc):
+    from paper_2006_12910_amd import lb
+    a, b = (_domain(lb, nx, ny, storage, kw, two, disc) for two in (1, 0))
+    ta, tb = _times((a, b), n)
+    assert ta < 1.15 * tb, (ta / tb, ta / (4 * n) * 1e6, tb / (4 * n) * 1e6)
+    a.close()
+    b.close()
