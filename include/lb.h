@@ -306,8 +306,8 @@ lb_status lb_set_particle_state(lb_domain *d, const lb_particle_state *in, int32
 #define LB_OPT_FORCE_AVERAGE 5
 /* 1 (default): a domain without particles and pressure faces, with native
  * arithmetic (the power law: with a wall or obstacles and without noise),
- * advances 3, 5, 7 or 9 time steps per launch, as many as suit its size; the
- * steps between stay in on-chip memory -- bit-identical to single steps, with
+ * advances 3, 5, 7 or 9 time steps per launch, as many as suit its size and
+ * collision (single steps where those are faster); the steps between stay in on-chip memory -- bit-identical to single steps, with
  * the launch and the memory traffic paid once for all of them.  So does one
  * with a single particle, three steps per launch, if its radius is at most 8,
  * its box fits the domain and LB_OPT_OVERLAP is off.  0: single

@@ -11,7 +11,6 @@
 #include <mutex>
 #include <new>
 #include <string>
-#include <tuple>
 #include <vector>
 
 #include "lb.h"
@@ -202,50 +201,8 @@ struct GraphCache {
   }
 };
 
-// Several steps per launch: the region (sweepn_impl.h) and the most steps.
-struct MultiPlan {
-  int k = 0, nmax = 1;
-};
-
-int multi_tiles(int k, int n, int nx, int ny) {
-  const int ow = region(k).cw - 2 * (n - 1), oh = region(k).rs - 2 * (n - 1);
-  return ((nx + ow - 1) / ow) * ((ny + oh - 1) / oh);
-}
-
-// Region and steps per launch for the domains of one launch, (nx, ny) each:
-// the least time a step by the model of sweepn_impl.h.  v, us a wave-row (64
-// nodes) of vector issue, fitted to 2048^2 and 512^2 lattices: FP32 0.054 (the
-// power law 0.09, noise 0.10), FP16 0.061, FP64 0.07; a launch alone on its CU
-// takes 8 v a step (1.0 us a step at 7 steps on 128 x 64, 1.37 with the power
-// law) and 4 us.  The model is within 10 % of the measured times from 48 x 33
-// to 4096^2, FP32 and FP64, and within 15 % for FP16; the second-best choice is
-// rarely more than that behind.
-MultiPlan choose_multi(int storage, int feat, const std::vector<std::pair<int, int>> &sizes) {
-  const double v = (storage == LB_F64 ? 0.07 : storage == LB_F32 ? 0.054 : 0.061) +
-                   ((feat & F_POWER) ? 0.035 : 0.0) + ((feat & F_NOISE) ? 0.046 : 0.0);
-  MultiPlan best;
-  double least = 1e300;
-  for (int k = 0; k < REGIONS; ++k) {
-    if (!region_fits(storage, k)) continue;
-    const Region g = region(k);
-    for (int n = 3; n <= MULTI_MAX; n += 2) {
-      const int ow = g.cw - 2 * (n - 1), oh = g.rs - 2 * (n - 1);
-      if (ow < 4 || oh < 4) continue;
-      double tiles = 0.0;
-      for (const auto &s : sizes) tiles += multi_tiles(k, n, s.first, s.second);
-      double waves = 0.0;
-      for (int s = 0; s < n; ++s) waves += g.cw * (g.rs - 2 * s) / 64.0;
-      const double bytes = tiles * 9 * storage_bytes(storage) * ((double)g.cw * g.rs + ow * oh);
-      const double us = 4.0 + std::max({n * 8.0 * v, std::ceil(tiles / 256.0) * v * waves,
-                                        bytes >= 2 * (double)(256 << 20) ? bytes / 5e6 : 0.0});
-      if (us / n < least) {
-        least = us / n;
-        best.k = k;
-        best.nmax = n;
-      }
-    }
-  }
-  return best;
+StepKind kind_of(const lb_domain_desc *d) {
+  return StepKind{d->storage, d->kT > 0.0, d->power_law != 0, plm_of(d->n_index)};
 }
 
 }  // namespace
@@ -392,19 +349,15 @@ struct MultiSteps {
   uint32_t *arrived = nullptr;            // and its counter of workgroups
   const lb_batch *batch = nullptr;        // or the batch
   bool disc = false;                      // with particles
-  int tiles(int n) const { return batch ? batch->multi_tiles[n] : multi_tiles(plan.k, n, one->nx, one->ny); }
+  int tiles(int n) const { return batch ? batch->multi_tiles[n] : multi_tiles(plan.k[n], n, one->nx, one->ny); }
   const int *prefix(int n) const { return batch ? batch->dprefixn(n) : nullptr; }
 };
 
-// Enqueue n steps, several a launch.  The launches take odd numbers of steps
-// (1: the single-step sweep), as few and as equal as possible: k parts of lo
-// or lo + 2 with k n_max >= n and k of n's parity.  Launched one by one, not
-// from a captured graph: a launch runs 7 us and more, longer than the host
-// takes to enqueue it, and captured chunks of fixed lengths would break the
+// Enqueue n steps, several a launch, as split_steps has it.  Launched one by
+// one, not from a captured graph: a launch runs 7 us and more, longer than the
+// host takes to enqueue it, and captured chunks of fixed lengths would break the
 // calls into shorter launches (250 steps: 48 launches and 10 counter updates
-// instead of 36 and 1).  With n_max 3, two single steps beside a part of 3 become
-// one of 5 (32 steps of 24 FP16 domains: ten launches of 3 and two of
-// 1, 2.65 ms; nine of 3 and one of 5, 2.57).
+// instead of 36 and 1).
 //
 // With particles a launch takes DISC_STEPS; single steps, the last of the call,
 // are k_pre, the sweep and k_post, with the post pass of one and the pre pass of
@@ -419,33 +372,23 @@ constexpr int ADVANCE_BLOCKS = 64;
 lb_status run_multi(const StepPlan &p, const MultiSteps &m, int64_t n, hipStream_t s) {
   for (int64_t done = 0; done < n;) {
     const int c = (int)std::min<int64_t>(n - done, 1 << 16);
-    int parts = (c + m.plan.nmax - 1) / m.plan.nmax;
-    if ((parts ^ c) & 1) ++parts;
-    int lo = c / parts;
-    if (!(lo & 1)) --lo;
-    int longer = (c - parts * lo) / 2, longest = 0;
-    if (!m.disc && lo == 1 && m.plan.nmax == 3) {
-      longest = std::min(longer, (parts - longer) / 2);
-      parts -= 2 * longest;
-      longer -= longest;
-    }
-    const bool one = m.one != nullptr && m.plan.k == 0 && !m.disc;
+    const StepSplit r = split_steps(c, m.plan);
     bool advanced = false;
-    for (int i = 0, k = 0; i < parts; ++i) {
-      const int len = lo + (i < longest ? 4 : i < longest + longer ? 2 : 0);
-      if (one) {
+    for (int i = 0, k = 0; i < r.parts; ++i) {
+      const int len = r.len(i);
+      if (m.one != nullptr && m.plan.k[len] == 0 && !m.disc) {
         const int tiles = m.tiles(len);
-        advanced = i + 1 == parts && tiles <= ADVANCE_BLOCKS;
+        advanced = i + 1 == r.parts && tiles <= ADVANCE_BLOCKS;
         p.ks->multi_one(m.one, m.arrived, k, len, advanced ? c : 0, tiles, s);
       } else if (m.disc && len > 1) {
         p.ks->multi_disc(p.doms, m.prefix(len), p.ndom, p.items, p.nitems, m.one, k, m.tiles(len), s);
       } else if (m.disc) {
-        if (i == longer) p.ks->pre(p.doms, p.items, p.nitems, k, s);
+        if (i == r.longer) p.ks->pre(p.doms, p.items, p.nitems, k, s);
         p.ks->sweep(p.doms, p.prefix, p.ndom, k, p.blocks, 0, s);
-        if (i + 1 < parts) p.ks->post_pre(p.doms, p.items, p.nitems, k, s);
+        if (i + 1 < r.parts) p.ks->post_pre(p.doms, p.items, p.nitems, k, s);
         else p.ks->post(p.doms, p.items, p.nitems, k, s);
       } else if (len > 1)
-        p.ks->multi(p.doms, m.prefix(len), p.ndom, m.plan.k, k, len, m.tiles(len), s);
+        p.ks->multi(p.doms, m.prefix(len), p.ndom, m.plan.k[len], k, len, m.tiles(len), s);
       else
         p.ks->sweep(p.doms, p.prefix, p.ndom, k, p.blocks, 0, s);
       k += len;
@@ -568,7 +511,7 @@ lb_status run_steps(GraphCache &gc, bool use_graph, int chunk, hipStream_t strea
   return LB_OK;
 }
 
-// Several steps a launch serve domains without particles whose kernel set
+// Several steps a launch can serve domains without particles whose kernel set
 // has the kernel (native arithmetic), unless switched off with
 // LB_OPT_TWO_STEP: with periodic edges or walls held as solid label rows (the
 // tiles wrap around the domain), and no density face.
@@ -599,8 +542,8 @@ bool disc_fits(const lb_domain *d, const std::vector<PState> &all) {
 
 MultiPlan disc_plan(int storage) {
   MultiPlan p;
-  p.k = disc_region(storage);
   p.nmax = DISC_STEPS;
+  p.k[DISC_STEPS] = disc_region(storage);
   return p;
 }
 
@@ -759,7 +702,7 @@ static lb_status lb_create_domain_impl(const lb_domain_desc *desc, void *dev_wor
   set_tiles(h, default_tile_w(desc->nx), desc->storage >= LB_F16_DELTA ? 4 : 2);
   h.stream_stores = sweep_working_set(h) >= STREAM_STORE_MIN_BYTES;
   d->rows2 = two_step_rows(h.storage);
-  d->multi = choose_multi(h.storage, feat, std::vector<std::pair<int, int>>{{desc->nx, desc->ny}});
+  d->multi = choose_multi(kind_of(desc), Sizes{{desc->nx, desc->ny}});
   h.rho0 = desc->rho0;
   h.tau = desc->power_law ? desc->tau_min : desc->tau;
   h.omega = 1.0 / h.tau;
@@ -1098,7 +1041,7 @@ static lb_status lb_step_impl(lb_domain *d, int64_t nsteps) {
       p.ntiles = d->ntiles();
     }
     lb_status s;
-    if (multi_ok(d)) {
+    if (multi_ok(d) && d->multi.nmax > 1) {
       MultiSteps m;
       m.plan = d->multi;
       m.one = &d->hd;
@@ -1577,8 +1520,7 @@ static lb_status lb_batch_create_impl(lb_domain *const *domains, int32_t n, void
   std::vector<int> prefix(batch_prefixes(n), 0);
   std::vector<PItem> items;
   bool multi = b->ks.multi != nullptr;
-  std::vector<std::pair<int, int>> sizes;
-  int feat = 0;
+  Sizes sizes;
   for (int i = 0; i < n; ++i) {
     descs[i] = domains[i]->hd;
     prefix[i + 1] = prefix[i] + domains[i]->ntiles();
@@ -1587,16 +1529,14 @@ static lb_status lb_batch_create_impl(lb_domain *const *domains, int32_t n, void
     multi = multi && (multi_ok(domains[i]) || disc_ok(domains[i]));
     b->disc = b->disc || domains[i]->np > 0;
     sizes.emplace_back(domains[i]->desc.nx, domains[i]->desc.ny);
-    feat |= domains[i]->feat;
   }
-  b->multi_step = multi && !(b->disc && b->ks.multi_disc == nullptr);
   b->multi = b->disc ? disc_plan(domains[0]->desc.storage)
-                     : choose_multi(domains[0]->desc.storage, feat, sizes);
-  const int longest = b->multi.nmax == 3 ? 5 : b->multi.nmax;  // see run_multi
-  for (int len = 3; len <= longest; len += 2) {
+                     : choose_multi(kind_of(&domains[0]->desc), sizes);
+  b->multi_step = multi && !(b->disc && b->ks.multi_disc == nullptr) && b->multi.nmax > 1;
+  for (int len = 3; len <= b->multi.longest(); len += 2) {
     int *pre = prefix.data() + (size_t)(len + 1) / 2 * (n + 1);
     for (int i = 0; i < n; ++i)
-      pre[i + 1] = pre[i] + multi_tiles(b->multi.k, len, sizes[i].first, sizes[i].second);
+      pre[i + 1] = pre[i] + multi_tiles(b->multi.k[len], len, sizes[i].first, sizes[i].second);
     b->multi_tiles[len] = pre[n];
   }
   // the members' common value if they agree, else the default

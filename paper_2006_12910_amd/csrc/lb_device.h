@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "step_plan.h"
+
 namespace lbk {
 
 // ---------------------------------------------------------------------------
@@ -44,7 +46,6 @@ __host__ __device__ constexpr int basis_poly(int k, int i) {
 
 // ---------------------------------------------------------------------------
 enum : int { BC_PERIODIC = 0, BC_WALL = 1, BC_PRESSURE = 2 };
-enum : int { ST_F64 = 0, ST_F32 = 1, ST_F16 = 2, ST_BF16 = 3 };
 
 // Feature bits of a sweep instantiation.
 enum : int {
@@ -56,23 +57,7 @@ enum : int {
   F_FAVG = 32,     // particle update with the mean of two steps' forces (runtime only)
   F_TRT = 64,      // two-relaxation-time collision (never with F_NOISE)
 };
-// Power-law exponent specialisations.
-enum : int { PL_GENERIC = 0, PL_HALF = 1, PL_3Q = 2, PL_3H = 3 };
 
-// Regions of the launches of several steps (sweepn_impl.h): columns, rows,
-// threads (a whole number of nodes each).  The small
-// one has the shortest step (one node a thread, two waves a SIMD) and the
-// most tiles; the middle one fills a CU with two workgroups; the large one has
-// the least rim, and suits the formats whose LDS leaves room for two.
-struct Region {
-  int cw, rs, nt;
-};
-constexpr int REGIONS = 3;
-__host__ __device__ constexpr Region region(int k) {
-  return k == 0 ? Region{32, 16, 512} : (k == 1 ? Region{32, 32, 512} : Region{64, 32, 512});
-}
-// the large region of 8-byte values would take 147 KB of LDS
-constexpr bool region_fits(int storage, int k) { return !(storage == ST_F64 && k == 2); }
 // Threads per region.  FP16 domains with labels take a thread per two nodes of
 // the large one: 64 registers, so two workgroups of 16 waves a CU, all that it
 // can hold (a thread per four: 106 registers, 16 waves).  Us a step, before and
@@ -87,7 +72,6 @@ __host__ __device__ constexpr int multi_threads(int storage, int k, int feat) {
              ? 1024
              : region(k).nt;
 }
-constexpr int MULTI_MAX = 9;  // most steps a launch takes
 
 // Steps per launch of domains with one particle (discn_impl.h), the tiles'
 // region, and the largest sides of the particle's label box and own region.

@@ -16,11 +16,8 @@
 // What this is for.  Small lattices are bound by the ~4 us that a launch
 // costs from its first load to its last store, large ones by the bytes of a
 // step: both are paid once per n steps.  What n costs is the rim, computed by
-// several workgroups: a launch takes about
-//   4 us + max(n 8 v, ceil(tiles / 256) v waves),  v = 0.05 to 0.1 us,
-// waves the wave-rows of all its steps (vector issue of one CU), or its bytes
-// at 5 TB/s; choose_multi in lb_api.hip takes the region and n that this
-// makes smallest.
+// several workgroups.  choose_multi in step_plan.h takes the region and n whose
+// time a step is smallest by its model of a launch.
 //
 // n is odd (3, 5, 7, 9): the launch reads buffer T & 1 and writes the other,
 // which is the buffer of step T + n, so any sequence of launches and single

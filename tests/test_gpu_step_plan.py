@@ -48,6 +48,10 @@ POWER = lambda n: dict(bc_y="wall", power_law=dict(n=n, K=0.01))
     ("f64", POWER(1.3), 2048, 2048, 30, False),  # the generic exponent's pow: registers
     ("f64", POWER(1.3), 2048, 1024, 8, False),
     ("f64", POWER(1.3), 2048, 2048, 6, True),
+    ("f16", dict(kT=1e-5), 2048, 2048, 8, False),  # a launch of five in place of three single steps
+    ("f16", dict(kT=1e-5, obstacles=True), 2048, 2048, 8, False),
+    ("bf16", POWER(0.75), 2048, 2048, 8, False),
+    ("f32", dict(), 2048, 2048, 8, False),
 ])
 def test_several_steps_a_launch_are_not_slower_than_single_ones(storage, kw, nx, ny, n, disc):
     from paper_2006_12910_amd import lb
