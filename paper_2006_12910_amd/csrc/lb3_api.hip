@@ -12,6 +12,7 @@
 #include "host_read.h"
 #include "lb.h"
 #include "launch3.h"
+#include "step_plan3.h"
 
 using namespace lbk3;
 
@@ -34,12 +35,6 @@ lb_status fail3(lb_status s, const std::string &msg) { return lbk::lb_fail(s, ms
   } while (0)
 
 size_t al256(size_t v) { return (v + 255) & ~size_t(255); }
-
-// The sweep streams past the 256 MB last-level cache when both buffers exceed
-// it by half (192 x 192 x nz, us a step cached / streaming at 290, 360, 400,
-// 450 MB: FP32 57.8 / 58.3, 73.0 / 73.5, 78.4 / 74.4, 92.9 / 84.4; FP64 with
-// noise 54.5 / 60.0, 72.1 / 76.6, 76.8 / 76.8, 92.3 / 87.5).
-constexpr size_t STREAM_MIN_BYTES = size_t(384) << 20;
 
 // nodes per host-transfer band (initial fields, moments, populations)
 constexpr long long BAND = 262144;
@@ -291,8 +286,7 @@ static lb_status lb3_create_domain_impl(const lb3_domain_desc *desc, void *dev_w
   h.key1 = (uint32_t)(desc->seed >> 32);
   h.tiles_x = (desc->nx + 63) / 64;
   h.tiles_y = (desc->ny + 3) / 4;
-  h.stream = 2.0 * d->q * desc->nz * desc->ny * L.pitch * (double)elem_of(desc->storage) >=
-             (double)STREAM_MIN_BYTES;
+  h.stream = streams3(d->q, desc->nx, desc->ny, desc->nz, elem_of(desc->storage));
   h.rho0 = desc->rho0;
   // with the power law tau is the local tau*; the domain-wide values below
   // are those of tau_min (unused by the sweep)
