@@ -13,9 +13,8 @@ void sweep3_f32(const Dom3 &h, const Dom3 *dd, int q, bool wide, unsigned blocks
 void sweep3_f16(const Dom3 &h, const Dom3 *dd, int q, bool wide, unsigned blocks, int kstep, hipStream_t s);
 void sweep3_bf16(const Dom3 &h, const Dom3 *dd, int q, bool wide, unsigned blocks, int kstep, hipStream_t s);
 
-// two steps per launch (sweep3x2.hip), and whether they take less time than
-// two launches of one
-bool sweep3x2_pays(const Dom3 &h, int q);
-void launch_sweep3x2(const Dom3 &h, int q, int kstep, int which, hipStream_t s);
+// two steps per launch, FP32 and FP64 without noise: segments of `planes` planes
+// (split3)
+void launch_sweep3x2(const Dom3 &h, int q, int planes, int kstep, int which, hipStream_t s);
 
 }  // namespace lbk3

@@ -140,6 +140,7 @@ struct lb3_domain {
   int64_t t = 0;
   bool wide = false;               // the sweep takes 64-bit byte offsets
   int q = 19;                      // lattice velocities
+  int x2_planes = 0;               // two steps per launch: planes a segment of them, or 0
   std::vector<uint8_t> host_mask;  // [nz][ny][pitch]: walls and obstacles
   lbk::HostRing ring;              // pinned buffers of the host reads
   Dom3 *ddesc() const { return (Dom3 *)(ws + L.desc); }
@@ -226,11 +227,6 @@ void launch_sweep3(const lb3_domain *d, unsigned blocks, int k) {
   sweep(d->hd, d->ddesc(), d->q, d->wide, blocks, k, d->stream);
 }
 
-// The two-step sweep has 32-bit offsets and no noise.
-bool two_step3_ok(const lb3_domain *d) {
-  return !d->wide && !d->hd.noise && sweep3x2_pays(d->hd, d->q);
-}
-
 }  // namespace
 
 extern "C" {
@@ -305,6 +301,11 @@ static lb_status lb3_create_domain_impl(const lb3_domain_desc *desc, void *dev_w
   h.omega = 1.0 / h.tau;
   h.trt = desc->collision == LB3_TRT ? 1 : 0;
   h.noise = desc->kT > 0.0 ? 1 : 0;
+  // the two-step sweep has 32-bit offsets and no noise
+  if (!d->wide && !h.noise &&
+      two_steps_pay3(Kind3{desc->storage, d->q, L.solids, h.trt != 0, h.pl != 0, desc->n_index}, desc->nx,
+                     desc->ny, desc->nz))
+    d->x2_planes = split3(desc->storage, desc->nx, desc->ny, desc->nz).planes;
   h.kT = desc->kT;
   h.kT_f = (float)desc->kT;
   h.tau_m = h.trt ? 0.5 + desc->magic / (h.tau - 0.5) : h.tau;
@@ -392,16 +393,15 @@ static lb_status lb3_step_impl(lb3_domain *d, int64_t nsteps) {
   if (!d) return fail3(LB_EINVAL, "null domain");
   if (nsteps < 0) return fail3(LB_EINVAL, "nsteps < 0");
   const unsigned blocks = (unsigned)(d->hd.tiles_x * d->hd.tiles_y * d->desc.nz);
-  const bool two = two_step3_ok(d);
   for (int64_t k0 = 0; k0 < nsteps; k0 += 1024) {
     const int c = (int)std::min<int64_t>(1024, nsteps - k0);
     int k = 0;
     // four steps are a pair of two-step launches: the first leaves the state
     // in the buffer of the other parity, the second brings it back
-    if (two)
+    if (d->x2_planes > 0)
       for (; k + 4 <= c; k += 4) {
-        launch_sweep3x2(d->hd, d->q, k, 0, d->stream);
-        launch_sweep3x2(d->hd, d->q, k + 2, 1, d->stream);
+        launch_sweep3x2(d->hd, d->q, d->x2_planes, k, 0, d->stream);
+        launch_sweep3x2(d->hd, d->q, d->x2_planes, k + 2, 1, d->stream);
       }
     for (; k < c; ++k) launch_sweep3(d, blocks, k);
     hipLaunchKernelGGL(k_advance3, dim3(1), dim3(1), 0, d->stream, d->ddesc(), c);

@@ -10,8 +10,7 @@
 // wave per row of the first step (RY rows: the outputs and one on either
 // side) and one more for the two rim columns, so that rows stay 64 aligned
 // lanes and every store a whole line (62 output columns with the rim in lanes
-// 0 and 63, as the D2Q9 sweep has it, took a fifth more lanes on nx = 192 and
-// 256).  Every iteration computes the first step of one z plane from global
+// 0 and 63 took a fifth more lanes on nx = 192 and 256).  Every iteration computes the first step of one z plane from global
 // memory, exactly as k_sweep3 does, rounds it to the storage format, and
 // hands it to the neighbouring columns through LDS.  What a node pulls from
 // it completes the output plane behind it (e_z = -1) and starts the next two
@@ -28,16 +27,17 @@
 // bound by the memory path still.  RY = 15 (one workgroup of 16 waves a CU)
 // 95 open, 144 against 129 with solids; RY = 9, 11 between.
 //
-// As with the D2Q9 two-step sweep a launch leaves the state in the buffer of
-// the other parity, so launches come in pairs (`which` = 0 then 1).
+// A launch leaves the state in the buffer of the other parity, so launches come
+// in pairs (`which` = 0 then 1).
 #pragma once
 
+#include "step_plan3.h"
 #include "sweep3_impl.h"
 
 namespace lbk3 {
 
-// output columns of a tile, and of its first step: one more on either side
-constexpr int X2_COLS = 64, X2_PITCH = X2_COLS + 2;
+// columns of a tile's first step: one more on either side
+constexpr int X2_PITCH = X2_COLS + 2;
 
 // LDS planes of one workgroup: the directions with e_z = +1 twice (the plane
 // at hand and the one before), the other moving ones once.  A table: the

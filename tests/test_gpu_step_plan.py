@@ -1,5 +1,5 @@
-"""Several steps a launch against single steps (LB_OPT_TWO_STEP off), by the
-clock: on lattices that fill the GPU, where neither launches nor rounding
+"""Several steps a launch against single steps (LB_OPT_TWO_STEP off; in 3D, calls
+of three steps), by the clock: on lattices that fill the GPU, where neither launches nor rounding
 counts for much, the plan that the library takes by itself is not slower than
 the single steps it stands in for.  The bound leaves 15 % for the clock; the
 faults that these cases stand for cost 20 to 60 %."""
@@ -60,3 +60,29 @@ def test_several_steps_a_launch_are_not_slower_than_single_ones(storage, kw, nx,
     assert ta < 1.15 * tb, (ta / tb, ta / (4 * n) * 1e6, tb / (4 * n) * 1e6)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("lattice,n", [("d3q19", 0.75), ("d3q27", 0.75), ("d3q27", 1.3)])
+def test_two_step_3d_sweep_is_not_slower_than_single_steps(lattice, n):
+    import torch
+    from paper_2006_12910_amd import lb
+    nx, ny, nz = 160, 160, 96
+    rng = np.random.default_rng(3)
+    z, y, x = (np.arange(v).reshape(s) for v, s in ((nz, (-1, 1, 1)), (ny, (1, -1, 1)), (nx, (1, 1, -1))))
+    one = np.ones((nz, ny, nx))
+    init = (1.0, 0.02 * np.sin(2 * np.pi * z / nz) * one, 0.01 * np.cos(4 * np.pi * x / nx) * one,
+            0.01 * np.sin(4 * np.pi * y / ny) * one)
+    d = lb.Domain3(nx, ny, nz, tau=0.8, storage="f32", lattice=lattice, init=init,
+                   obstacles=rng.random((nz, ny, nx)) < 0.05, power_law=dict(n=n, K=0.01))
+    best = {3: 1e9, 12: 1e9}
+    for rep in range(9):
+        for c in best:
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(24 // c):
+                d.step(c)
+            torch.cuda.synchronize()
+            if rep:
+                best[c] = min(best[c], time.perf_counter() - t0)
+    assert best[12] < 1.15 * best[3], (best[12] / best[3], best)
+    d.close()
