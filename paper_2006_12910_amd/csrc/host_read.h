@@ -23,6 +23,23 @@
 
 namespace lbk {
 
+// Pinned memory is allocated and freed whatever another thread captures: a
+// capture in the global mode, torch's default, would otherwise be invalidated by
+// the first large read, or the destruction, of a domain beside it.
+class CaptureRelaxed {
+ public:
+  CaptureRelaxed() { swapped_ = hipThreadExchangeStreamCaptureMode(&mode_) == hipSuccess; }
+  ~CaptureRelaxed() {
+    if (swapped_) (void)hipThreadExchangeStreamCaptureMode(&mode_);
+  }
+  CaptureRelaxed(const CaptureRelaxed &) = delete;
+  CaptureRelaxed &operator=(const CaptureRelaxed &) = delete;
+
+ private:
+  hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+  bool swapped_;
+};
+
 // Pinned ring and events of one domain, made at its first large read and
 // given back with it: at most SLOTS * SLOT_BYTES.
 struct HostRing {
@@ -34,6 +51,7 @@ struct HostRing {
   // to the stream's device, whichever is current.
   bool ready(hipStream_t s) {
     if (ev[SLOTS - 1]) return true;
+    const CaptureRelaxed relaxed;
     int current = 0, device = 0;
     if (hipGetDevice(&current) != hipSuccess || hipStreamGetDevice(s, &device) != hipSuccess) {
       (void)hipGetLastError();
@@ -48,6 +66,7 @@ struct HostRing {
   HostRing(const HostRing &) = delete;
   HostRing &operator=(const HostRing &) = delete;
   ~HostRing() {
+    const CaptureRelaxed relaxed;
     for (int i = 0; i < SLOTS; ++i) {
       if (ev[i]) (void)hipEventDestroy(ev[i]);
       if (mem[i]) (void)hipHostFree(mem[i]);
