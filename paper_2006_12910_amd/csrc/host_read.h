@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <atomic>
 #include <condition_variable>
+#include <cstdint>
 #include <cstring>
 #include <mutex>
 #include <thread>
@@ -154,11 +155,13 @@ class HostCopiers {
       std::memcpy(h_[k] + n0, s + (long long)k * cnt, (size_t)cnt * 8);
   }
   void work(int w) {
-    // one write per page, until there is something to copy
+    // one write per page, until there is something to copy; of nothing, so
+    // that a read that fails leaves the arrays as they were (an addition: a load
+    // and a store would fault twice, into the shared page of zeros first)
     for (size_t k = (size_t)w; k < h_.size(); k += (size_t)step_)
       for (long long i = 0; i < n_; i += 512) {
         if (published_.load(std::memory_order_acquire) || stop_.load()) goto copies;
-        ((volatile double *)h_[k])[i] = 0.0;
+        __asm__ volatile("lock; addq $0, %0" : "+m"(*(uint64_t *)(h_[k] + i)));
       }
   copies:
     {
