@@ -379,8 +379,9 @@ lb_status lb_noise_normals(uint64_t seed, uint32_t domain_id, uint32_t step, uin
 /* Autotune this domain's sweep tiles: times each candidate single-step tile
  * width / rows-per-thread pair over `steps` single steps (LB_OPT_TWO_STEP off
  * while timing) and keeps the fastest; where several steps a launch apply,
- * `steps` of those are timed too.  The state advances by the steps timed.
- * *best_ms receives the best time per step. */
+ * `steps` (rounded up to a multiple of four) of those are timed after it.  The
+ * state advances by the steps timed.  *best_ms receives the time per step that
+ * the domain then runs at. */
 lb_status lb_autotune(lb_domain *d, int32_t steps, double *best_ms);
 
 /* A batch's tiles follow from its members' sizes: nothing is left to tune, the

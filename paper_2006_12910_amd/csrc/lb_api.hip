@@ -527,6 +527,11 @@ bool disc_ok(const lb_domain *d) {
          d->desc.bc_x != LB_PRESSURE;
 }
 
+// Whether lb_step takes several steps a launch.
+bool several_steps(const lb_domain *d) {
+  return (multi_ok(d) && d->multi.nmax > 1) || (disc_ok(d) && !d->overlap);
+}
+
 // The particle's radius and box against the region, and the region and the box
 // against the domain, which must not hold a node of either twice; a start
 // faster than what k_pre lets pass stays with the single steps.
@@ -1041,17 +1046,12 @@ static lb_status lb_step_impl(lb_domain *d, int64_t nsteps) {
       p.ntiles = d->ntiles();
     }
     lb_status s;
-    if (multi_ok(d) && d->multi.nmax > 1) {
+    if (several_steps(d)) {
       MultiSteps m;
-      m.plan = d->multi;
       m.one = &d->hd;
+      m.disc = d->np > 0;
+      m.plan = m.disc ? disc_plan(d->desc.storage) : d->multi;
       m.arrived = &d->dhdr()->arrived;
-      s = run_multi(p, m, nsteps, d->stream);
-    } else if (disc_ok(d) && !d->overlap) {
-      MultiSteps m;
-      m.plan = disc_plan(d->desc.storage);
-      m.one = &d->hd;
-      m.disc = true;
       s = run_multi(p, m, nsteps, d->stream);
     } else {
       s = run_steps(d->graphs, d->use_graph, d->chunk, d->stream, d->cap, p, nsteps);
@@ -1411,12 +1411,10 @@ static lb_status lb_autotune_impl(lb_domain *d, int32_t steps, double *best_ms) 
   if (s != LB_OK) return s;
   if ((s = lb_set_option(d, LB_OPT_TILE_WIDTH, bw)) != LB_OK) return s;
   if ((s = lb_set_option(d, LB_OPT_ROWS_PER_THREAD, br)) != LB_OK) return s;
-  if (multi_ok(d)) {
-    // several steps a launch: chosen by rule, timed for the report
-    double ms = 0.0;
+  if (several_steps(d)) {
+    // chosen by rule: timed for the report of what the domain runs at
     const int n4 = std::max(4, (steps + 3) / 4 * 4);
-    if ((s = time_steps([&](int64_t n) { return lb_step(d, n); }, d->stream, n4, &ms)) != LB_OK) return s;
-    best = std::min(best, ms);
+    if ((s = time_steps([&](int64_t n) { return lb_step(d, n); }, d->stream, n4, &best)) != LB_OK) return s;
   }
   if (best_ms) *best_ms = best;
   return check_health(d);
