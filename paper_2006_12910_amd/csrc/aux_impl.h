@@ -118,8 +118,9 @@ __global__ __launch_bounds__(256) void k_moments(const DevDomain D, double *rho_
     for (int i = 0; i < 9; ++i) {
       const double f = (double)S::dec(v[u][i], i);
       dr += f;
-      if (cx(i) != 0) jx += cx(i) > 0 ? f : -f;
-      if (cy(i) != 0) jy += cy(i) > 0 ? f : -f;
+      // a product with zero too: a non-finite population leaves no velocity
+      jx += f * cx(i);
+      jy += f * cy(i);
     }
     const double rho = D.rho0 + dr;
     rho_o[n[u]] = solid[u] ? 0.0 : rho;
