@@ -52,7 +52,8 @@ STORAGE_BYTES = {"f16": 2, "bf16": 2, "f32": 4}
 ROUNDING = {"f16": "stochastic", "bf16": "stochastic", "f32": "nearest"}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sweep_traffic.json")
 SWEEP_SOURCES = ["paper_2006_12910_amd/csrc/sweep_impl.h", "paper_2006_12910_amd/csrc/sweepn_impl.h",
-                 "paper_2006_12910_amd/csrc/lb_device.h", "paper_2006_12910_amd/csrc/kernels_st.h",
+                 "paper_2006_12910_amd/csrc/lb_device.h", "paper_2006_12910_amd/csrc/step_plan.h",
+                 "paper_2006_12910_amd/csrc/kernels_st.h",
                  "paper_2006_12910_amd/csrc/lb_api.hip", "paper_2006_12910_amd/build.py"]
 
 
@@ -701,9 +702,9 @@ def profile_entry(steps_per_launch):
 
 
 def traffic_entry(steps_per_launch):
-    """Measured HBM bytes per launch of the dominant sweep kernel, or None."""
+    """Measured HBM bytes per step of the dominant sweep kernel, or None."""
     t = profile_entry(steps_per_launch)
-    return None if t is None else t.get("hbm_bytes_per_launch")
+    return None if t is None else t.get("hbm_bytes_per_step")
 
 
 def main():
@@ -783,11 +784,11 @@ def main():
         spl = None if two else 1
         # average sweep time per step: the extra steps of the 2K-step call over
         # the K-step one (the per-call density sums cancel)
-        launch_ms = (ms2 - ms) / args.steps
+        step_ms = (ms2 - ms) / args.steps
         entry = {"mlups": round(mlups, 1), "mflups": round(mflups, 1), "ms_per_step": round(ms / args.steps, 4),
-                 "sweep_launch_ms": round(launch_ms, 4), "steps_per_launch": spl,
-                 "sweep_GBps": round(bytes_alg / (launch_ms * 1e-3) / 1e9, 1),
-                 "hbm_frac": round(bytes_alg / (launch_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
+                 "sweep_step_ms": round(step_ms, 4), "steps_per_launch": spl,
+                 "sweep_GBps": round(bytes_alg / (step_ms * 1e-3) / 1e9, 1),
+                 "hbm_frac": round(bytes_alg / (step_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                  "bytes_per_step": bytes_alg, "rounding": ROUNDING[v],
                  "two_step": two,
                  "tiles": tiles if isinstance(tiles, str) or tiles is None else {f"{'obstacles' if k[0] else 'open'}/class{k[1]}": f"{t[0]}x{t[1]}"
@@ -814,12 +815,12 @@ def main():
     roofline = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": traffic,
-                # bytes that really crossed HBM per launch (profiled) over the
-                # launch duration: with several steps per launch the algorithmic
-                # rate above is an effective one and exceeds this
+                # bytes that really crossed HBM per step (profiled) over the
+                # sweep's time per step: with several steps per launch the
+                # algorithmic rate above is an effective one and exceeds this
                 "measured_GBps": (None if traffic is None else
-                                  round(traffic / (head["sweep_launch_ms"] * 1e-3) / 1e9, 1)),
-                "launch_ms": head["sweep_launch_ms"],
+                                  round(traffic / (head["sweep_step_ms"] * 1e-3) / 1e9, 1)),
+                "step_ms": head["sweep_step_ms"],
                 "kernel": (f"k_multi (several steps per launch, {variants[0]} storage, batched)"
                            if spl is None else f"k_sweep ({variants[0]} storage, batched)"),
                 "steps_per_launch": spl,

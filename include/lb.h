@@ -473,7 +473,11 @@ lb_status lb3_set_obstacles(lb3_domain *d, const uint8_t *host_mask, size_t n);
  * the faster; bit-identical); nsteps >= 0. */
 lb_status lb3_step(lb3_domain *d, int64_t nsteps);
 /* rho and u = j/rho + g/2 at every node (zero on solids), host FP64
- * [nz][ny][nx] each.  Synchronises; LB_EUNSTABLE after a non-finite state. */
+ * [nz][ny][nx] each.  Reads of 8 MiB and more (these and the populations) go
+ * through 16 MiB of pinned host memory, allocated by the domain's first such
+ * read and held until it is destroyed, and up to four helper threads for the
+ * duration of the call; without either they are plain copies.  Synchronises;
+ * LB_EUNSTABLE after a non-finite state. */
 lb_status lb3_moments(lb3_domain *d, double *rho, double *ux, double *uy, double *uz);
 /* Post-collision deviations, host FP64 [q][nz][ny][nx].  Synchronises. */
 lb_status lb3_get_populations(lb3_domain *d, double *host_dev_f);
