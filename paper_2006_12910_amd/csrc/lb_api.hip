@@ -527,10 +527,10 @@ bool disc_ok(const lb_domain *d) {
          d->desc.bc_x != LB_PRESSURE;
 }
 
-// Whether lb_step takes several steps a launch.
-bool several_steps(const lb_domain *d) {
-  return (multi_ok(d) && d->multi.nmax > 1) || (disc_ok(d) && !d->overlap);
-}
+// Whether lb_step takes several steps a launch (or, where its plan has just one,
+// enqueues single steps as it would the others: a caller's capture holds them,
+// and none of the sweep path's graphs, which it could not).
+bool several_steps(const lb_domain *d) { return multi_ok(d) || (disc_ok(d) && !d->overlap); }
 
 // The particle's radius and box against the region, and the region and the box
 // against the domain, which must not hold a node of either twice; a start
@@ -1530,7 +1530,7 @@ static lb_status lb_batch_create_impl(lb_domain *const *domains, int32_t n, void
   }
   b->multi = b->disc ? disc_plan(domains[0]->desc.storage)
                      : choose_multi(kind_of(&domains[0]->desc), sizes);
-  b->multi_step = multi && !(b->disc && b->ks.multi_disc == nullptr) && b->multi.nmax > 1;
+  b->multi_step = multi && !(b->disc && b->ks.multi_disc == nullptr);
   for (int len = 3; len <= b->multi.longest(); len += 2) {
     int *pre = prefix.data() + (size_t)(len + 1) / 2 * (n + 1);
     for (int i = 0; i < n; ++i)
