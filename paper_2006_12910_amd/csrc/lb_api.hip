@@ -547,7 +547,7 @@ bool disc_fits(const lb_domain *d, const std::vector<PState> &all) {
 
 MultiPlan disc_plan(int storage) {
   MultiPlan p;
-  p.nmax = DISC_STEPS;
+  p.us[1] = p.us[DISC_STEPS] = 1.0;  // as many of DISC_STEPS as there are
   p.k[DISC_STEPS] = disc_region(storage);
   return p;
 }
@@ -707,7 +707,7 @@ static lb_status lb_create_domain_impl(const lb_domain_desc *desc, void *dev_wor
   set_tiles(h, default_tile_w(desc->nx), desc->storage >= LB_F16_DELTA ? 4 : 2);
   h.stream_stores = sweep_working_set(h) >= STREAM_STORE_MIN_BYTES;
   d->rows2 = two_step_rows(h.storage);
-  d->multi = choose_multi(kind_of(desc), Sizes{{desc->nx, desc->ny}});
+  d->multi = plan_multi(kind_of(desc), Sizes{{desc->nx, desc->ny}});
   h.rho0 = desc->rho0;
   h.tau = desc->power_law ? desc->tau_min : desc->tau;
   h.omega = 1.0 / h.tau;
@@ -1529,9 +1529,9 @@ static lb_status lb_batch_create_impl(lb_domain *const *domains, int32_t n, void
     sizes.emplace_back(domains[i]->desc.nx, domains[i]->desc.ny);
   }
   b->multi = b->disc ? disc_plan(domains[0]->desc.storage)
-                     : choose_multi(kind_of(&domains[0]->desc), sizes);
+                     : plan_multi(kind_of(&domains[0]->desc), sizes);
   b->multi_step = multi && !(b->disc && b->ks.multi_disc == nullptr);
-  for (int len = 3; len <= b->multi.longest(); len += 2) {
+  for (int len = 3; len <= MULTI_MAX && b->multi.us[len] < NEVER; len += 2) {
     int *pre = prefix.data() + (size_t)(len + 1) / 2 * (n + 1);
     for (int i = 0; i < n; ++i)
       pre[i + 1] = pre[i] + multi_tiles(b->multi.k[len], len, sizes[i].first, sizes[i].second);

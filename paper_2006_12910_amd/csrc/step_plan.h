@@ -39,14 +39,14 @@ struct StepKind {
   int plm;  // with power
 };
 
-// The most steps a launch takes (1: single steps), the region of the launches
-// of each number of steps (of one step: 0, or else the single-step sweep), and
-// whether one of five pays beside those of three.
+// Time of a launch of n steps (odd; 1: the single-step sweep) by the model, and
+// its region (of one step: 0, or else the single-step sweep); no such launch
+// where the time is NEVER.
+constexpr double NEVER = 1e300;
 struct MultiPlan {
-  int nmax = 1;
-  bool five = false;
+  double us[MULTI_MAX + 1];
   int k[MULTI_MAX + 1] = {};
-  int longest() const { return five ? 5 : nmax; }
+  MultiPlan() { std::fill(us, us + MULTI_MAX + 1, NEVER); }
 };
 
 using Sizes = std::vector<std::pair<int, int>>;  // nx, ny of every domain of a launch
@@ -106,65 +106,78 @@ inline double launch_us(const StepKind &c, int k, int n, const Sizes &sizes) {
   return 4.7 + std::max(n * chain[k] * v, std::hypot(busy * tile_rows * v, moved / rate));
 }
 
-// Whether the single steps of one domain, beside launches of several, run over
-// region 0 too: as long as every tile has a CU of its own (up to 64 of them the
-// launch also moves the counter on, k_multi_one), and up to the last-level cache
-// unless more than a third of the rows of the tiles lie outside.  Us a call of one step, single-step sweep /
-// region 0: 128 x 64 6.5 / 4.0, 724 x 700 FP16 with noise 12.2 / 9.2, 1031 x 1000
-// FP64 23.3 / 22.4; 20000 x 20 FP32 8.6 / 11.3.
+// Whether the single steps of one domain run over region 0 too: as long as every
+// tile has a CU of its own (up to 64 of them the launch also moves the counter
+// on, k_multi_one), and up to 17 rounds of the chip and the last-level cache,
+// unless more than a third of the rows of the tiles lie outside.  Us a call of
+// one step, single-step sweep / region 0: 128 x 64 6.5 / 4.0, 724 x 700 FP16 with
+// noise 12.2 / 9.2, 1031 x 1000 FP64 23.3 / 22.4, 1448^2 FP16 16.6 / 15.9, 2048^2 FP16
+// with noise 38.4 / 42.1; 20000 x 20 FP32 8.6 / 11.3.
 inline bool single_in_region(const StepKind &c, int nx, int ny) {
   const double bytes = c.storage == ST_F64 ? 8 : c.storage == ST_F32 ? 4 : 2;
   const int tiles = multi_tiles(0, 1, nx, ny);
-  return tiles <= 256 || (18 * bytes * nx * ny <= 256e6 && tiles * 8.0 <= 1.35 * ((nx + 63) / 64) * ny);
+  return tiles <= 256 || (tiles <= 17 * 256 && 18 * bytes * nx * ny <= 256e6 &&
+                          tiles * 8.0 <= 1.35 * ((nx + 63) / 64) * ny);
 }
 
-// Steps a launch for the domains of one launch: the least time a step, the
-// region of each number of steps likewise.  Single steps where nothing is
-// less: 16-bit formats with noise on lattices that fill the chip issue no fewer
-// instructions in a tile than in a single step, and the rim comes on top (FP16
-// 2048^2: 41.3 against 38.4).
-//
-// Beside launches of three, two single steps and a part of three become one
-// of five where that is faster: FP16 with obstacles 2048^2, 116 us against 133,
-// but with noise 226 against 204 (always five gained 2.5 % on 32 steps of 24
-// FP16 domains, and lost 15 % of 8 steps with noise or a power law).
-inline MultiPlan choose_multi(const StepKind &c, const Sizes &sizes) {
+// The launches for the domains of one launch, each over the region that takes
+// the least time.
+inline MultiPlan plan_multi(const StepKind &c, const Sizes &sizes) {
   MultiPlan p;
-  double us[MULTI_MAX + 1];
-  us[1] = launch_us(c, 0, 1, sizes);
-  for (int n = 3; n <= MULTI_MAX; n += 2) {
-    us[n] = 1e300;
+  p.us[1] = launch_us(c, 0, 1, sizes);
+  p.k[1] = sizes.size() == 1 && single_in_region(c, sizes[0].first, sizes[0].second) ? 0 : 1;
+  for (int n = 3; n <= MULTI_MAX; n += 2)
     for (int k = 0; k < REGIONS; ++k) {
       if (!region_fits(c.storage, k) || std::min(region(k).cw, region(k).rs) - 2 * (n - 1) < 4) continue;
       const double t = launch_us(c, k, n, sizes);
-      if (t < us[n]) us[n] = t, p.k[n] = k;
+      if (t < p.us[n]) p.us[n] = t, p.k[n] = k;
     }
-    if (us[n] / n < us[p.nmax] / p.nmax) p.nmax = n;
-  }
-  p.k[1] = sizes.size() == 1 && single_in_region(c, sizes[0].first, sizes[0].second) ? 0 : 1;
-  p.five = p.nmax == 3 && us[5] < us[3] + 2 * us[1];
   return p;
 }
 
-// c steps in parts of an odd number of steps each (1: the single-step sweep),
-// as few and as equal as possible: of lo, lo + 2 or, beside parts of three and
-// one, five.  The longest come first.
+// c steps in parts of an odd number of steps each, the longest first: of lo,
+// lo + 2 and, beside parts of three and one, five.
 struct StepSplit {
   int parts, lo, longer, longest;
   int len(int i) const { return lo + (i < longest ? 4 : i < longest + longer ? 2 : 0); }
-};
-inline StepSplit split_steps(int c, const MultiPlan &p) {
-  StepSplit r{(c + p.nmax - 1) / p.nmax, 0, 0, 0};
-  if ((r.parts ^ c) & 1) ++r.parts;
-  r.lo = c / r.parts;
-  if (!(r.lo & 1)) --r.lo;
-  r.longer = (c - r.parts * r.lo) / 2;
-  if (p.five && r.lo == 1) {
-    r.longest = std::min(r.longer, (r.parts - r.longer) / 2);
-    r.parts -= 2 * r.longest;
-    r.longer -= r.longest;
+  double us(const MultiPlan &p) const {
+    return (longest ? longest * p.us[lo + 4] : 0.0) + (longer ? longer * p.us[lo + 2] : 0.0) +
+           (parts - longer - longest) * p.us[lo];
   }
-  return r;
+};
+
+// The cheapest of the splits into parts of at most 1, 3, .. steps, as few and as
+// equal as each of those allows, and of the one into five, three and one in
+// which two single steps and a part of three became one of five.  Single steps
+// alone where nothing is less: 16-bit formats with noise on lattices that fill
+// the chip issue no fewer instructions in a tile than in a single step, and the
+// rim comes on top (FP16 2048^2: 41.3 us a step against 38.4).  The five pays for
+// FP16 with obstacles at 2048^2, 116 us against 133, but not with noise, 226
+// against 204 (always taken it gained 2.5 % on 32 steps of 24 FP16 domains, and
+// lost 15 % of 8 steps with noise or a power law).
+inline StepSplit split_steps(int c, const MultiPlan &p) {
+  StepSplit best{};
+  double least = 2 * NEVER;
+  auto take = [&](const StepSplit &r) {
+    const double t = r.us(p);
+    if (t < least) least = t, best = r;
+  };
+  for (int n = 1; n <= MULTI_MAX; n += 2) {
+    if (!(p.us[n] < NEVER)) break;
+    StepSplit r{(c + n - 1) / n, 0, 0, 0};
+    if ((r.parts ^ c) & 1) ++r.parts;
+    r.lo = c / r.parts;
+    if (!(r.lo & 1)) --r.lo;
+    r.longer = (c - r.parts * r.lo) / 2;
+    take(r);
+    if (n == 3 && r.lo == 1 && p.us[5] < NEVER) {
+      r.longest = std::min(r.longer, (r.parts - r.longer) / 2);
+      r.parts -= 2 * r.longest;
+      r.longer -= r.longest;
+      take(r);
+    }
+  }
+  return best;
 }
 
 }  // namespace lbk

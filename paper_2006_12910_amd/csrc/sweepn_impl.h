@@ -16,8 +16,8 @@
 // What this is for.  Small lattices are bound by the ~4 us that a launch
 // costs from its first load to its last store, large ones by the bytes of a
 // step: both are paid once per n steps.  What n costs is the rim, computed by
-// several workgroups.  choose_multi in step_plan.h takes the region and n whose
-// time a step is smallest by its model of a launch.
+// several workgroups.  step_plan.h has a model of what a launch costs and splits
+// the steps of a call by it.
 //
 // n is odd (3, 5, 7, 9): the launch reads buffer T & 1 and writes the other,
 // which is the buffer of step T + n, so any sequence of launches and single

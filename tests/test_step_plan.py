@@ -11,13 +11,17 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SOURCE = """
 #include "step_plan.h"
 using namespace lbk;
-extern "C" void plan(int st, int noise, int power, int plm, int nx, int ny, int *out) {
-  const MultiPlan p = choose_multi(StepKind{st, noise != 0, power != 0, plm}, Sizes{{nx, ny}});
-  out[0] = p.k[p.nmax], out[1] = p.nmax, out[2] = p.five, out[3] = p.k[3], out[4] = p.k[5];
+// the launches of a call of c steps: how many of each length, and the regions
+extern "C" int plan(int st, int noise, int power, int plm, int nx, int ny, int c, int *len, int *k) {
+  const MultiPlan p = plan_multi(StepKind{st, noise != 0, power != 0, plm}, Sizes{{nx, ny}});
+  const StepSplit r = split_steps(c, p);
+  for (int i = 0; i < r.parts; ++i) len[i] = r.len(i), k[i] = p.k[len[i]];
+  return r.parts;
 }
-extern "C" int split(int c, int nmax, int five, int *len) {
+// with launches of up to nmax steps alone, of the same time a step each
+extern "C" int split(int c, int nmax, int *len) {
   MultiPlan p;
-  p.nmax = nmax, p.five = five != 0;
+  for (int n = 1; n <= nmax; n += 2) p.us[n] = n == nmax || n == 1 ? 1.0 : n == 3 ? 2.0 : 3.0;
   const StepSplit r = split_steps(c, p);
   for (int i = 0; i < r.parts; ++i) len[i] = r.len(i);
   return r.parts;
@@ -55,35 +59,53 @@ def planner(tmp_path_factory):
     return C.CDLL(str(lib))
 
 
-def _plan(planner, name):
+def _launches(planner, name, c):
     storage, kind, size = name.split()
     nx, ny = (int(v) for v in size.split("x"))
     plm = {"pl13": 0, "pl5": 1, "pl75": 2}.get(kind, 0)
-    out = (C.c_int * 5)()
-    planner.plan(["f64", "f32", "f16", "bf16"].index(storage), "noise" in kind, "pl" in kind, plm, nx, ny, out)
-    return out[0], out[1], bool(out[2]), out[3], out[4]
+    lens, regions = (C.c_int * 4096)(), (C.c_int * 4096)()
+    parts = planner.plan(["f64", "f32", "f16", "bf16"].index(storage), "noise" in kind, "pl" in kind, plm,
+                         nx, ny, c, lens, regions)
+    return lens[:parts], regions[:parts]
+
+
+def _splits(c):
+    """The splits that the plan chooses among: parts as few and as equal as a
+    largest one allows, and five in place of one of three and two of one."""
+    out = []
+    for n in range(1, 10, 2):
+        parts = -(-c // n)
+        parts += (parts ^ c) & 1
+        lo = c // parts
+        lo -= 1 - lo % 2
+        longer = (c - parts * lo) // 2
+        lens = [lo + 2] * longer + [lo] * (parts - longer)
+        out.append(lens)
+        if n == 3 and lo == 1:
+            f = min(longer, (parts - longer) // 2)
+            out.append([5] * f + [3] * (longer - f) + [1] * (parts - longer - 2 * f))
+    return out
 
 
 @pytest.mark.parametrize("name,times", MEASURED)
-def test_choice_is_near_the_best_measured_one(planner, name, times):
-    k, n, five, k3, k5 = _plan(planner, name)
-    chosen = times[(k, n) if n > 1 else (1, 1)] / n
-    best = min(t / key[1] for key, t in times.items())
-    assert chosen <= 1.10 * best, (name, k, n, chosen, best)
-    if n == 3:  # a launch of five against one of three and two single steps
-        us5, us311 = times[(k5, 5)], times[(k3, 3)] + 2 * times[(1, 1)]
-        assert (us5 if five else us311) <= 1.10 * min(us5, us311), (name, five, us5, us311)
+def test_splits_are_near_the_best_measured_ones(planner, name, times):
+    best_of = {n: min(t for (_, m), t in times.items() if m == n) for n in {m for _, m in times}}
+    for c in (1, 2, 3, 4, 6, 8, 12, 16, 25, 50, 100, 250):
+        lens, regions = _launches(planner, name, c)
+        assert sum(lens) == c
+        if any((k, n) not in times for n, k in zip(lens, regions) if n > 1):
+            continue  # not measured: seven and nine steps on large lattices
+        us = sum(times[(k, n) if n > 1 else (1, 1)] for n, k in zip(lens, regions))
+        best = min(sum(best_of[n] for n in s) for s in _splits(c) if all(n in best_of for n in s))
+        assert us <= 1.12 * best, (name, c, lens, us, best)
 
 
-@pytest.mark.parametrize("nmax,five", [(3, 0), (3, 1), (5, 0), (7, 0), (9, 0)])
-def test_splits_are_odd_parts_that_add_up(planner, nmax, five):
+@pytest.mark.parametrize("nmax", [1, 3, 5, 7, 9])
+def test_splits_are_odd_parts_that_add_up(planner, nmax):
     buf = (C.c_int * 4096)()
     for c in list(range(1, 200)) + [1023, 1024, 1025]:
-        parts = planner.split(c, nmax, five, buf)
+        parts = planner.split(c, nmax, buf)
         lens = buf[:parts]
-        assert sum(lens) == c and all(v % 2 == 1 and v >= 1 for v in lens)
-        assert max(lens) <= (5 if five else nmax)
+        assert sum(lens) == c and all(v % 2 == 1 and 1 <= v <= nmax for v in lens)
         assert lens == sorted(lens, reverse=True)
-        assert parts <= -(-c // nmax) + 1  # as few as odd parts allow
-        if not five:
-            assert max(lens) - min(lens) <= 2
+        assert parts <= -(-c // nmax) + 2
